@@ -193,3 +193,24 @@ def test_hard_decide_extreme_inputs(ctx):
     ref = oracle.hard_decisions(X, lab, Y)
     np.testing.assert_array_equal(dec.cpu().numpy().astype(np.uint32), ref["decided"])
     c.close()
+
+
+@pytest.mark.parametrize("M,D", [(32, 2), (64, 4), (256, 13), (2048, 8), (4096, 12)])
+@pytest.mark.parametrize("twins", [False, True])
+def test_hard_decide_ties_across_tiles(ctx, M, D, twins):
+    # one, two and many point tiles; received points at midpoints of pairs of
+    # points (near points in other tiles, other rows of the tile and other lane
+    # halves), and sets in which every point occurs twice, M / 2 labels apart:
+    # the lower label of an exact tie is decided
+    rng = np.random.default_rng(7 * M + D)
+    X, lab = inputs.random_constellation(M + D, M, D)
+    if twins:
+        pos = np.empty(M, dtype=np.int64)
+        pos[lab] = np.arange(M)
+        X[pos[M // 2:]] = X[pos[:M // 2]]
+    a = rng.integers(0, M, 500)
+    b = rng.integers(0, M, 500)
+    mid = ((X[a] + X[b]) / 2.0).astype(np.float32)
+    noisy = (X[a] + 0.3 * rng.standard_normal((500, D))).astype(np.float32)
+    _decide_exact(ctx, X, lab, np.concatenate([mid, noisy, X[b].astype(np.float32)]),
+                  np.concatenate([a, b, a]).astype(np.int64))
