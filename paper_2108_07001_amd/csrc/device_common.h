@@ -420,4 +420,143 @@ __device__ __forceinline__ double wave_sum(double x) {
   return x;
 }
 
+// ---- exact recomputation by a whole wave ------------------------------------
+// The exact path of the second tiers where few lanes of a wave need it. A lane
+// that walks a large set alone holds its wave for ~0.5 ms per item (8-D, M =
+// 2048: two passes over half the set per starved side), and the few waves
+// that hold such items end the launch alone; here the 64 lanes share each
+// pass over the points, one item after another. 8-D/2048, 1e6 samples with
+// LLRs: 484 such items at 24 dB, 3.86 -> 1.00 ms; 1969 at 25 dB, 9.01 ->
+// 1.06 ms. Same metric and reference point as the per-lane form above; the
+// sums are taken per lane and then across the lanes.
+
+// Index of the point nearest to received point n (n, tl uniform); ties to the lowest.
+template <int D>
+__device__ __noinline__ int wave_nearest(const float* __restrict__ in, int sweep, const float* __restrict__ xl,
+                                         int M, float sigma, int64_t n, int tl) {
+  float y[D];
+  reload_point<float, D>(in, sweep, xl, sigma, n, tl, y);
+  int best = 0;
+  float bd = __builtin_inff();
+  for (int j = threadIdx.x & 63; j < M; j += 64) {
+    const float d2 = sqdist<float, D>(y, xl + (int64_t)j * D);
+    if (d2 < bd) { bd = d2; best = j; }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const float od = __shfl_xor(bd, off, 64);
+    const int oj = __shfl_xor(best, off, 64);
+    if (od < bd || (od == bd && oj < best)) { bd = od; best = oj; }
+  }
+  return __builtin_amdgcn_readfirstlane(best);
+}
+
+// As slow_rel, for uniform n, tl, r, k, b: log2 sum over the selection of
+// 2^(a_j - a_r), or a_t - a_r itself (k = -2).
+template <int D>
+__device__ __noinline__ float wave_rel(const float* __restrict__ in, int sweep, const float* __restrict__ xl, int M,
+                                       float sigma, float c, int64_t n, int tl, int r, int k, int b) {
+  float y[D];
+  reload_point<float, D>(in, sweep, xl, sigma, n, tl, y);
+  const float* xr = xl + (int64_t)r * D;
+  if (k == -2) return rel_metric<float, D>(y, xr, xl + (int64_t)tl * D, c);
+  const int cnt = k >= 0 ? M >> 1 : M;
+  const int lowmask = k >= 0 ? (1 << k) - 1 : 0;
+  auto label = [&](int i) { return k >= 0 ? (((i & ~lowmask) << 1) | (b << k) | (i & lowmask)) : i; };
+  const int lane = threadIdx.x & 63;
+  float dmax = -__builtin_inff();
+  for (int i = lane; i < cnt; i += 64) {
+    const float dj = rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c);
+    dmax = dj > dmax ? dj : dmax;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    const float o = __shfl_xor(dmax, off, 64);
+    dmax = o > dmax ? o : dmax;
+  }
+  float sum = 0.0f;
+  for (int i = lane; i < cnt; i += 64)
+    sum += Real<float>::exp2(rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c) - dmax);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  return dmax + Real<float>::log2(sum);
+}
+
+// Outputs of the lanes' FP32-family items (`mine`: this lane holds one) from
+// sums in the FP64 frame 2^(a + K64) (the second tiers); called by all lanes
+// of a wave together. Entries below thr64 are recomputed exactly relative to
+// the nearest point r and put back in the frame by adding K64 + a_r; if the
+// total itself is below thr64 every entry is recomputed and all stay relative
+// to a_r. lt_t is log2 of the transmitted point's own term in the frame (used
+// when tl >= 0 and the total is not recomputed). Only the starved entries cost
+// a pass over the constellation. The caller counts the items.
+template <int D>
+__device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
+                                                     double total, double (&side)[2 * kMaxBits], double thr64,
+                                                     int K64, double lt_t, float* llr_out, float& u, float& v) {
+  unsigned long long todo = __ballot(mine);
+  if (!todo) return;
+  // A pass costs the lanes' own form M points however many of them hold an
+  // item, and this one M / 64 points and the call, the sample's loads and the
+  // exchanges (as much as ~8 points) per item.
+  if (__builtin_popcountll(todo) * ((a.M >> 6) + 8) >= a.M) {
+    if (mine) finish_item_frame64<D>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
+    return;
+  }
+  const int m = a.m;
+  const int lane = threadIdx.x & 63;
+  const uint32_t redo = mine ? exact_entries<double>(total, side, m, thr64) : 0u;
+  const bool total_slow = !(total >= thr64);
+  double lam_tot = log2_wide(total), delta_t = 0.0;
+  while (todo) {
+    const int src = __builtin_ctzll(todo);
+    todo &= todo - 1ull;
+    const int64_t ns = (int64_t)(((uint64_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)n >> 32), src) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((uint32_t)n, src));
+    const int ts = __builtin_amdgcn_readlane(tl, src);
+    uint32_t rs = __builtin_amdgcn_readlane(redo, src);
+    const bool all = __builtin_amdgcn_readlane(total_slow ? 1 : 0, src) != 0;
+    const int r = wave_nearest<D>(a.in, a.sweep, a.xl, a.M, a.sigma, ns, ts);
+    double base = 0.0;
+    if (all) {
+      const double lt = (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, -1, 0);
+      const double dt =
+          ts >= 0 ? (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, -2, 0) : 0.0;
+      if (lane == src) {
+        lam_tot = lt;
+        delta_t = dt;
+      }
+    } else {
+      float y[D];
+      reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, ns, ts, y);
+      base = (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
+    }
+    while (rs) {
+      const int i = __builtin_ctz(rs);
+      rs &= rs - 1u;
+      const double lam =
+          base + (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, i >> 1, i & 1);
+      // (a chain of selects: no index into the lane's array)
+#pragma unroll
+      for (int e = 0; e < 2 * kMaxBits; ++e) side[e] = (e == i && lane == src) ? lam : side[e];
+    }
+  }
+  if (mine) {
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < kMaxBits; ++k)
+      if (k < m) {
+        // recomputed entries hold their logarithm, the others the sum
+        const double l0 = ((redo >> (2 * k)) & 1u) ? side[2 * k] : log2_wide(side[2 * k]);
+        const double l1 = ((redo >> (2 * k + 1)) & 1u) ? side[2 * k + 1] : log2_wide(side[2 * k + 1]);
+        if (llr_out) llr_out[k] = (float)(0.6931471805599453094 * (l0 - l1));
+        acc += lam_tot - (((tl >> k) & 1) ? l1 : l0);
+      }
+    if (tl >= 0) {
+      u = (float)(total_slow ? lam_tot - delta_t : lam_tot - lt_t);
+      v = (float)acc;
+    }
+  }
+}
+
 }  // namespace air

@@ -784,16 +784,14 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
   }
   // beyond the FP64 window: the starved entries take the exact path; a
   // sample side outside the f16 range leaves no usable entry, so all do
-  if (flagged && st2 && h == 0) {
-    if (smp.ovf) {
-      total = 0.0;
+  const bool mine = flagged && st2 && h == 0;
+  if (mine && smp.ovf) {
+    total = 0.0;
 #pragma unroll
-      for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
-    }
-    finish_item_frame64<D>(ex, smp.n, smp.tl, total, side, thr64, K64, log2_wide(val64(arg_t)), lout, u,
-                           v);
+    for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
   }
-  return flagged && st2 && h == 0;
+  finish_items_frame64<D>(ex, mine, smp.n, smp.tl, total, side, thr64, K64, log2_wide(val64(arg_t)), lout, u, v);
+  return mine;
 }
 
 // Second tier: the flagged samples, 32 to a tile (the SNR points' runs, each

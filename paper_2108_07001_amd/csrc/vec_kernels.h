@@ -369,10 +369,18 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
     const bool has = pos - start < (uint64_t)cnt;
     items += (unsigned long long)__builtin_popcountll(__ballot(has));
     bool ex_lane = false;
+    int64_t n = 0;
+    int tl = -1;
+    double side[2 * kMaxBits];
+#pragma unroll
+    for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
+    double total = 0.0, lt_t = 0.0;
+    float* lout = nullptr;
+    float u = 0.f, v = 0.f;
     if (has) {
-      const int64_t n = (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)];
+      n = (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)];
       // flagged samples are live: a transmitted index, if any, is in range
-      const int tl = a.tx ? (int)a.lab[a.tx[n]] : -1;
+      tl = a.tx ? (int)a.lab[a.tx[n]] : -1;
       const float c = a.snr.cf[s];
       float y[D];
       load_point<float, D>(a, n, tl, a.snr.sigmaf[s], y);
@@ -381,7 +389,6 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
       double hi0[NL], hi1[NL], node[NL];
 #pragma unroll
       for (int l = 0; l < NL; ++l) { hi0[l] = 0.0; hi1[l] = 0.0; node[l] = 0.0; }
-      double total = 0.0;
       for (int g = 0; g < NG; ++g) {
         const float* __restrict__ xg = xl + (int64_t)g * (G * D);
         double e[G];
@@ -411,9 +418,6 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
         }
         if (!placed) total = carry;
       }
-      double side[2 * kMaxBits];
-#pragma unroll
-      for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
 #pragma unroll
       for (int k = 0; k < LG; ++k) {
         double s0 = 0.0, s1 = 0.0;
@@ -433,14 +437,13 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
         }
       }
       // log2 of the transmitted point's own term as it entered the sums
-      const double lt_t =
+      lt_t =
           tl >= 0 ? log2_wide(val64(__builtin_fmaf(-c, sqdist<float, D>(y, xl + (int64_t)tl * D), K))) : 0.0;
       double smin = total;
 #pragma unroll
       for (int i = 0; i < 2 * kMaxBits; ++i)
         if (i < 2 * m) smin = __builtin_fmin(smin, side[i]);
-      float* lout = llr ? llr + (int64_t)s * a.llr_stride_s + n * m : nullptr;
-      float u = 0.f, v = 0.f;
+      lout = llr ? llr + (int64_t)s * a.llr_stride_s + n * m : nullptr;
       if (smin >= thr64) {
         const double lt = log2_wide(total);
         double vacc = 0.0;
@@ -455,17 +458,16 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
         u = (float)(lt - lt_t);
         v = (float)vacc;
       } else {
-        ExactArgs<float> ex = exact_args<float>(a, s);
-        finish_item_frame64<D>(ex, n, tl, total, side, thr64, K64, lt_t, lout, u, v);
         ex_lane = true;
       }
-      if (tl >= 0) {
-        const double du = (double)u, dv = (double)v;
-        au += du;
-        av += dv;
-        auu = __builtin_fma(du, du, auu);
-        avv = __builtin_fma(dv, dv, avv);
-      }
+    }
+    finish_items_frame64<D>(exact_args<float>(a, s), ex_lane, n, tl, total, side, thr64, K64, lt_t, lout, u, v);
+    if (has && tl >= 0) {
+      const double du = (double)u, dv = (double)v;
+      au += du;
+      av += dv;
+      auu = __builtin_fma(du, du, auu);
+      avv = __builtin_fma(dv, dv, avv);
     }
     exact += (unsigned long long)__builtin_popcountll(__ballot(ex_lane));
   }

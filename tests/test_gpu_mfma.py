@@ -264,3 +264,27 @@ def test_set_stream_orders_the_workspace(ctx):
     torch.cuda.synchronize()
     for st in outs:
         assert np.array_equal(st.cpu().numpy(), ref, equal_nan=True)
+
+
+@pytest.mark.parametrize("M,D", [(16, 2), (64, 4), (256, 5), (2048, 8), (4096, 12)])
+@pytest.mark.parametrize("k", [1, 7, 40])
+@pytest.mark.parametrize("prec", PRECS + ["fp32"])
+def test_exact_items_few_and_many_per_wave(ctx, M, D, k, prec):
+    # k received points far from every constellation point (the total is
+    # beyond both tiers' frames) and, at this SNR, others with single bit sides
+    # beyond them: few such items in a wave are finished by the whole wave,
+    # many by their own lanes
+    X, lab = inputs.random_constellation(M + D, M, D)
+    tx, z = inputs.random_block(M, M, 130, D)
+    snr = 27.0
+    Y = (X[tx] + math.sqrt(oracle.sigma2(X, snr)) * z.astype(np.float64)).astype(np.float32)
+    Y[3:3 + k] += 30.0
+    c = ctx.const(X, lab)
+    stats, L = ctx.mi_gmi(c, to_dev(Y), tx_dev(tx), snr, prec=prec, llr=True)
+    ctx.sync()
+    assert ctx.last_exact() >= k
+    ref = oracle.evaluate(X, lab, Y.astype(np.float64), snr, tx=tx)
+    assert_llr(L.cpu().numpy(), ref["llr"], 1e-3)
+    # the far samples' terms run to 1e5 bits: the same relative bar
+    assert_stats(stats.cpu().numpy(), ref["stats"], tol=1e-3 * max(1.0, np.abs(ref["stats"][:2]).max()), se_rel=2e-2)
+    c.close()
