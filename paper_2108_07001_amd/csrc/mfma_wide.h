@@ -109,6 +109,70 @@ struct WideSums {
       if (!placed) tot = carry;
     }
   }
+  // The run-time-M form of the sums takes four tiles at a time (M >= 128):
+  // tile() adds one tile's terms to R (zeroed first) and returns the tile's
+  // total, quad() hands the four totals of tiles 4 q ... 4 q + 3 to the levels,
+  // the two lowest in straight code, the others by the counter. Every sum is
+  // formed in the order in which add() forms it.
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) R[e] = 0.f;
+  }
+  __device__ __forceinline__ float tile(float (&ev)[NE]) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) R[e] += ev[e];
+    // the additions take place here (they would be moved behind the levels'
+    // branches, with every tile's terms held until there)
+    pin(R);
+#pragma unroll
+    for (int w2 = NE / 2; w2 >= 1; w2 >>= 1)
+#pragma unroll
+      for (int e = 0; e < w2; ++e) ev[e] = ev[2 * e] + ev[2 * e + 1];
+    return ev[0];
+  }
+  // (both groups together: one set of branches)
+  static __device__ __forceinline__ void pin(float (&r)[16]) {
+    asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]),
+                      "+v"(r[8]), "+v"(r[9]), "+v"(r[10]), "+v"(r[11]), "+v"(r[12]), "+v"(r[13]), "+v"(r[14]),
+                      "+v"(r[15]));
+  }
+  static __device__ __forceinline__ void quad(WideSums& A, WideSums& B, const float (&a)[4], const float (&b)[4],
+                                              int q, int ntb) {
+    static_assert(LV >= 2, "four tiles at least");
+    float ca, cb;
+    A.low2(a, ca);
+    B.low2(b, cb);
+    bool placed = false;
+#pragma unroll
+    for (int l = 2; l < LV; ++l) {
+      if (!placed && l < ntb) {
+        if ((q >> (l - 2)) & 1) {
+          A.g0[l] += A.gn[l];
+          A.g1[l] += ca;
+          ca = A.gn[l] + ca;
+          B.g0[l] += B.gn[l];
+          B.g1[l] += cb;
+          cb = B.gn[l] + cb;
+        } else {
+          A.gn[l] = ca;
+          B.gn[l] = cb;
+          placed = true;
+        }
+      }
+    }
+    if (!placed) {
+      A.tot = ca;
+      B.tot = cb;
+    }
+  }
+  __device__ __forceinline__ void low2(const float (&c)[4], float& carry) {
+    g0[0] = (g0[0] + c[0]) + c[2];
+    g1[0] = (g1[0] + c[1]) + c[3];
+    const float p0 = c[0] + c[1], p1 = c[2] + c[3];
+    g0[1] += p0;
+    g1[1] += p1;
+    carry = p0 + p1;
+  }
 };
 
 // Per-lane bit-side sums of the exact-size forms with one or two point tiles
@@ -396,6 +460,20 @@ __device__ __forceinline__ float softplus2(float x) {
   return __builtin_fmaxf(x, 0.0f) + Real<float>::log2(1.0f + Real<float>::exp2(-ax));
 }
 
+// The point loop of the run-time-M sums with the products a tile ahead: a
+// wave issues the next tile's products between the current tile's exponentials
+// and its sums, and the counter's two lowest levels are formed in straight
+// code, four tiles per step. Before, each tile began with its products and
+// waited ~150 cycles for them, and each took ~10 taken branches of the
+// counter: the VALU was busy 78 % of the time with two waves per SIMD (8-D
+// and 12-D), now 94 % (its instructions are the bound: 16 exponentials at two
+// slots and 31 additions per 16 points). 12-D/4096 rates (N = 1.6e7, 41 SNR
+// points) 427 -> 354 ms, 8-D/2048 first tier 13.2 -> 10.6 ms; M = 128 1.03x,
+// M = 512 1.13x. The four-chunk half-precision form (D = 16) spills with it
+// and measured 0.94-0.98x: it keeps the plain loop.
+template <int D, bool BF>
+constexpr bool w_pipe(int MB, bool ML) { return MB == 0 && !ML && (BF || mfma_nk(D, BF) <= 3); }
+
 // ML: the max-log form. Each bit side keeps the largest exponent instead of
 // the sum of the terms; the LLR is ln 2 times the difference of the two
 // sides' maxima, the GMI term is the BMD rate of those LLRs taken as exact,
@@ -404,7 +482,7 @@ __device__ __forceinline__ float softplus2(float x) {
 // sum can starve). Samples whose operands leave the operand range are done
 // by maxlog_direct.
 template <int D, bool BF, bool TBL, int MB, bool ML = false>
-__global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 ? 2 : 1)) void demap_mfma_w(const DemapArgs a,
+__global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>(MB, ML) ? 2 : 1)) void demap_mfma_w(const DemapArgs a,
                                                     const typename MfmaOp<BF>::vec* __restrict__ rec,
                                                     const float* __restrict__ xl) {
   typedef typename MfmaOp<BF>::vec V;
@@ -427,6 +505,11 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 ? 2 : 1)) void d
   // forming them here (at high SNR nearly every sample of a large set has a
   // bit side below the FP32 frame, and the first tier's work on it is lost)
   constexpr bool DIRECT = MB == 0 && !ML;
+  // run-time-M forms of the sums: four tiles per step of the point loop, the
+  // products a tile ahead (w_pipe); two sets of point records in registers
+  // where they fit into 256 with the rest
+  constexpr bool PIPE = w_pipe<D, BF>(MB, ML);
+  constexpr int NSET = D <= 12 ? 2 : 1;
   extern __shared__ double acc_lds[];      // [waves][S][4], then the tables (TBL)
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
@@ -553,7 +636,48 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 ? 2 : 1)) void d
         sA.init();
         sB.init();
       }
-      {
+      if constexpr (PIPE) {
+        sA.zero();
+        sB.zero();
+        // records of tiles t + 1 and t + 2 held at entry of step t, so that
+        // each product chain is issued while the previous tile's sums run,
+        // and each record load has two tiles to arrive (past the end the
+        // tiles wrap: those products are not used)
+        V rs[NSET][NK];
+        auto load = [&](V (&A)[NK], int t) {
+          const V* rp = rec_row<BF, HALF, NK>(tb.rec, t, j, h);
+#pragma unroll
+          for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
+        };
+        load(rs[0], 0);
+        if (NSET == 2) load(rs[NSET - 1], 1);
+        float16_t accA = opA.product(rs[0]);
+        float16_t accB = opB.product(rs[0]);
+        load(rs[0], NSET);
+        for (int t = 0; t < NT; t += 4) {
+          float cA[4], cB[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
+            float ev[NE];
+#pragma unroll
+            for (int e = 0; e < NE; ++e) ev[e] = Real<float>::exp2(accA[e]);
+            accA = opA.product(A);
+            cA[u] = sA.tile(ev);
+            // one group's terms in registers at a time
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) ev[e] = Real<float>::exp2(accB[e]);
+            accB = opB.product(A);
+            load(A, (t + u + 1 + NSET) & (NT - 1));
+            // keeps the loads here (else merged into loads before their use)
+            asm volatile("" ::: "memory");
+            cB[u] = sB.tile(ev);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          WideSums<NE, LV, ML>::quad(sA, sB, cA, cB, t >> 2, ntb);
+        }
+      } else {
         V A[NK];
         const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
 #pragma unroll
