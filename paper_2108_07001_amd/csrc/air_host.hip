@@ -486,7 +486,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
       if (e != hipSuccess) return hip_fail(ctx, e, "second-tier launch");
     }
     hipLaunchKernelGGL(finish_kernel, dim3(ns), dim3(256), 0, ctx->stream, ctx->partials,
-                       tier2 ? ctx->t2_partials : nullptr, grid, t2_grid(grid), N, c->M, c->m,
+                       tier2 ? ctx->t2_partials : nullptr, grid, t2_grid(grid, c->M), N, c->M, c->m,
                        stats ? stats + 4 * s0 : nullptr, ctx->call, next, ctx->sticky, maxlog ? 1 : 0);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "reduction kernel launch");

@@ -498,8 +498,11 @@ __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, 
   if (!todo) return;
   // A pass costs the lanes' own form M points however many of them hold an
   // item, and this one M / 64 points and the call, the sample's loads and the
-  // exchanges (as much as ~8 points) per item.
-  if (__builtin_popcountll(todo) * ((a.M >> 6) + 8) >= a.M) {
+  // exchanges per item, ~480 instructions or as many points as those take at
+  // ~3 D + 8 each (D = 1, M = 2048, 32 items per wave: 27.2 against 23.0 ms for
+  // the lanes' form, so the line there lies near 27 items).
+  constexpr int kCall = 480 / (3 * D + 8);
+  if (__builtin_popcountll(todo) * ((a.M >> 6) + kCall) >= a.M) {
     if (mine) finish_item_frame64<D>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
     return;
   }

@@ -548,6 +548,52 @@ struct TileSums {
     }
     if (!placed) tot = carry;
   }
+  // Four tiles at a time (sums of sets of 128 points and more): tile() adds
+  // one tile's terms to R (zeroed first) and returns the tile's total, quad()
+  // hands the totals of tiles 4 q ... 4 q + 3 to the levels, the two lowest in
+  // straight code. Every sum is formed in the order in which add() forms it.
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) R[e] = 0;
+  }
+  __device__ __forceinline__ F tile(F (&ev)[NE]) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) R[e] += ev[e];
+    // the additions take place here (they would be moved behind the levels'
+    // branches, with every tile's terms held until there)
+    static_assert(NE == 16, "pinned element by element");
+    asm volatile("" : "+v"(R[0]), "+v"(R[1]), "+v"(R[2]), "+v"(R[3]), "+v"(R[4]), "+v"(R[5]), "+v"(R[6]), "+v"(R[7]),
+                      "+v"(R[8]), "+v"(R[9]), "+v"(R[10]), "+v"(R[11]), "+v"(R[12]), "+v"(R[13]), "+v"(R[14]),
+                      "+v"(R[15]));
+#pragma unroll
+    for (int w2 = NE / 2; w2 >= 1; w2 >>= 1)
+#pragma unroll
+      for (int e = 0; e < w2; ++e) ev[e] = ev[2 * e] + ev[2 * e + 1];
+    return ev[0];
+  }
+  __device__ __forceinline__ void quad(const F (&c)[4], int q, int ntb) {
+    g0[0] = (g0[0] + c[0]) + c[2];
+    g1[0] = (g1[0] + c[1]) + c[3];
+    const F p0 = c[0] + c[1], p1 = c[2] + c[3];
+    g0[1] += p0;
+    g1[1] += p1;
+    F carry = p0 + p1;
+    bool placed = false;
+#pragma unroll
+    for (int l = 2; l < kTileLevels; ++l) {
+      if (!placed && l < ntb) {
+        if ((q >> (l - 2)) & 1) {
+          g0[l] += gn[l];
+          g1[l] += carry;
+          carry = gn[l] + carry;
+        } else {
+          gn[l] = carry;
+          placed = true;
+        }
+      }
+    }
+    if (!placed) tot = carry;
+  }
   // Combine with the other lane half of the sample: side[2k + b] and total,
   // identical in both halves (a + b in one, b + a in the other).
   __device__ __forceinline__ void combine(int ntb, F (&side)[2 * kMaxBits], F& total) const {
@@ -687,7 +733,7 @@ __device__ __forceinline__ void tier1_tile(const SampleTile<D, BF>& smp, const T
 // flagged finish it here, or on the exact path when even this frame starves
 // (or the sample side left the f16 range). Returns whether this lane took the
 // exact path.
-template <int D, bool BF, bool HALF, bool PF2 = false>
+template <int D, bool BF, bool HALF, bool QUAD = false>
 __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const Tables<BF>& tb,
                                            const ExactArgs<float>& ex, bool has_tx, bool flagged,
                                            int j, int h, int m, int NT, int ntb, float* lout,
@@ -707,7 +753,7 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
   };
   TileSums<double, NE> ts;
   ts.init();
-  if constexpr (!PF2) {
+  if constexpr (!QUAD) {
     V A[NK];
     const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
 #pragma unroll
@@ -725,34 +771,41 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
       ts.add(ev, t, ntb);
     }
   } else {
-    // PF2: point records two tiles ahead (two register sets used in turn):
-    // one tile's work does not cover an L2 read when the records are not in
-    // LDS (the second tier of a launch; the serving kernels keep one, to stay
-    // within their register budget)
-    V A0[NK], A1[NK];
-    const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
+    // QUAD (M >= 128): four tiles per step, the products a tile ahead and the
+    // point records NSET tiles ahead (one tile's work does not cover an L2 read;
+    // past the end the tiles wrap, and those products are not used). Bound by
+    // VALU issue: 16 terms take 131 instructions (148 with a tile at a time,
+    // whose counter branches and waits for the products left the VALU idle
+    // 23 % of the time; now 13 %). 8-D/2048, 9.7e6 items: 6.95 -> 6.4 ms.
+    constexpr int NSET = NK <= 2 ? 2 : 1;
+    ts.zero();
+    V rs[NSET][NK];
+    auto load = [&](V (&A)[NK], int t) {
+      const V* rp = rec_row<BF, HALF, NK>(tb.rec, t, j, h);
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) A0[kk] = rp[2 * kk];
-    if (NT > 1) {
-      const V* rq = rec_row<BF, HALF, NK>(tb.rec, 1, j, h);
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) A1[kk] = rq[2 * kk];
-    }
-    auto tile = [&](V (&A)[NK], int t) {
-      const float16_t acc = smp.product(A);
-      if (t + 2 < NT) {
-        const V* rq = rec_row<BF, HALF, NK>(tb.rec, t + 2, j, h);
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) A[kk] = rq[2 * kk];
-      }
-      double ev[NE];
-#pragma unroll
-      for (int e = 0; e < NE; ++e) ev[e] = val64(acc[e]);
-      ts.add(ev, t, ntb);
+      for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
     };
-    for (int t = 0; t < NT; t += 2) {
-      tile(A0, t);
-      if (t + 1 < NT) tile(A1, t + 1);
+    load(rs[0], 0);
+    if (NSET == 2) load(rs[NSET - 1], 1);
+    float16_t acc = smp.product(rs[0]);
+    load(rs[0], NSET);
+    for (int t = 0; t < NT; t += 4) {
+      double ct[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
+        double ev[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) ev[e] = val64(acc[e]);
+        __builtin_amdgcn_sched_barrier(0);
+        acc = smp.product(A);
+        load(A, (t + u + 1 + NSET) & (NT - 1));
+        // keeps the loads here (else merged into loads before their use)
+        asm volatile("" ::: "memory");
+        ct[u] = ts.tile(ev);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      ts.quad(ct, t >> 2, ntb);
     }
   }
   const float arg_t = has_tx ? smp.transmitted_arg(tb.rec, j, h) : 0.f;
@@ -800,8 +853,8 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
 // round-robin, so the work is spread evenly whatever waves of the first tier
 // listed it; each wave sums its samples per SNR point, and the block reduces
 // its waves in a fixed order.
-template <int D, bool BF, bool HALF, bool TBL>
-__global__ __launch_bounds__(256, D <= 12 ? 2 : 1) void demap_mfma_t2(const DemapArgs a,
+template <int D, bool BF, bool HALF, bool TBL, bool QUAD>
+__global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
                                                      const typename MfmaOp<BF>::vec* __restrict__ rec,
                                                      const float* __restrict__ xl) {
   typedef typename MfmaOp<BF>::vec V;
@@ -904,7 +957,7 @@ __global__ __launch_bounds__(256, D <= 12 ? 2 : 1) void demap_mfma_t2(const Dema
     float u, v;
     ExactArgs<float> ex = exact_args<float>(a, s);
     ex.xl = tb.xl;
-    const bool ex_lane = tier2_tile<D, BF, HALF, true>(smp, tb, ex, a.tx != nullptr, flagged, j, h, m, NT, ntb,
+    const bool ex_lane = tier2_tile<D, BF, HALF, QUAD>(smp, tb, ex, a.tx != nullptr, flagged, j, h, m, NT, ntb,
                                                  lout, u, v);
     exact += (unsigned long long)__builtin_popcountll(__ballot(ex_lane));
     if (flagged && h == 0 && smp.tl >= 0) {

@@ -984,13 +984,15 @@ hipError_t launch_mfma_wide_td(const DemapArgs& a, const void* rec, int grid, co
   }
   const hipStream_t st = l.stream;
   launch_t2_collect(a, grid, st);
-  const dim3 g2(t2_grid(grid));
+  const dim3 g2(t2_grid(grid, a.M));
   if (a.M == 16)
-    hipLaunchKernelGGL((demap_mfma_t2<D, BF, true, true>), g2, dim3(256), acc + tbytes, st, a, r, x);
+    hipLaunchKernelGGL((demap_mfma_t2<D, BF, true, true, false>), g2, dim3(256), acc + tbytes, st, a, r, x);
+  else if (a.M < 128)                      // one or two point tiles
+    hipLaunchKernelGGL((demap_mfma_t2<D, BF, false, true, false>), g2, dim3(256), acc + tbytes, st, a, r, x);
   else if (tbl)
-    hipLaunchKernelGGL((demap_mfma_t2<D, BF, false, true>), g2, dim3(256), acc + tbytes, st, a, r, x);
+    hipLaunchKernelGGL((demap_mfma_t2<D, BF, false, true, true>), g2, dim3(256), acc + tbytes, st, a, r, x);
   else
-    hipLaunchKernelGGL((demap_mfma_t2<D, BF, false, false>), g2, dim3(256), acc, st, a, r, x);
+    hipLaunchKernelGGL((demap_mfma_t2<D, BF, false, false, true>), g2, dim3(256), acc, st, a, r, x);
   return hipGetLastError();
 }
 

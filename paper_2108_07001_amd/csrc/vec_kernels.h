@@ -493,7 +493,7 @@ hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml
     if (!a.t2_items || !a.t2_tot || !a.t2_partials) return hipErrorInvalidValue;
     if constexpr (sizeof(T) == 4) {
       launch_t2_collect(a, grid, l.stream);
-      hipLaunchKernelGGL((demap_vec_t2<D, G>), dim3(t2_grid(grid)), dim3(kBlock), acc, l.stream, a,
+      hipLaunchKernelGGL((demap_vec_t2<D, G>), dim3(t2_grid(grid, a.M)), dim3(kBlock), acc, l.stream, a,
                          static_cast<const float*>(a.xl));
     }
     return hipGetLastError();

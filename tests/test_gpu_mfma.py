@@ -288,3 +288,20 @@ def test_exact_items_few_and_many_per_wave(ctx, M, D, k, prec):
     # the far samples' terms run to 1e5 bits: the same relative bar
     assert_stats(stats.cpu().numpy(), ref["stats"], tol=1e-3 * max(1.0, np.abs(ref["stats"][:2]).max()), se_rel=2e-2)
     c.close()
+
+
+@pytest.mark.parametrize("M,D,N", [(128, 1, 65), (128, 13, 200), (256, 16, 131), (512, 14, 97), (2048, 15, 70),
+                                   (4096, 4, 64)])
+@pytest.mark.parametrize("prec", PRECS)
+def test_point_loops_of_four_tiles(ctx, M, D, N, prec):
+    # the smallest set of the four-tile loops (one step, no counter levels), every
+    # number of levels above it, and the record layouts of D > 12; both tiers
+    # (at the high points every item belongs to the second)
+    X, lab = inputs.random_constellation(3 * M + D, M, D)
+    tx, z = inputs.random_block(5 * N + M, M, N, D)
+    w = inputs.Workload("t", X, lab, tx, z, np.array([2.0, 14.0, 21.0, 30.0]))
+    st, L = _sweep(ctx, w, prec)
+    ref = oracle.sweep(X, lab, tx, z, w.snr_db)
+    _report(f"M{M} D{D} N{N} {prec}", st, L, ref)
+    assert_stats(st, ref["stats"], se_rel=2e-2)
+    assert_llr(L, ref["llr"], LLR_BAR[prec])
