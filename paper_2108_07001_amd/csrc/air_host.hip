@@ -18,9 +18,10 @@ namespace air {
 
 // Vector-kernel launchers, one per (type, D), defined in vec_inst_*.hip
 // (arguments: launch, grid, where, max-log form, part: 0 the first tier, 1
-// the FP32 second tier).
-using VecFn = hipError_t (*)(const DemapArgs&, int, const Launch&, bool, int);
-#define AIR_DECL(tag, D) hipError_t launch_vec_##tag##_d##D(const DemapArgs&, int, const Launch&, bool, int);
+// the FP32 second tier; the next call's words where no reduction follows).
+using VecFn = hipError_t (*)(const DemapArgs&, int, const Launch&, bool, int, CallWords*);
+#define AIR_DECL(tag, D) \
+  hipError_t launch_vec_##tag##_d##D(const DemapArgs&, int, const Launch&, bool, int, CallWords*);
 #define AIR_DECL_ALL(tag)                                                                        \
   AIR_DECL(tag, 1) AIR_DECL(tag, 2) AIR_DECL(tag, 3) AIR_DECL(tag, 4) AIR_DECL(tag, 5)          \
   AIR_DECL(tag, 6) AIR_DECL(tag, 7) AIR_DECL(tag, 8) AIR_DECL(tag, 9) AIR_DECL(tag, 10)         \
@@ -104,9 +105,9 @@ static int mfma_grid(int64_t N) {
 // M >= 32 points take up to kMaxGrid blocks; for the small sets, whose
 // samples are cheap, the per-block reductions weigh more and 1024 blocks
 // measured faster (2-D QAM-4 buffers of 2^20 symbols: 1536 blocks, 25 %
-// slower).
-static int vec_grid(int64_t N, int M = 0) {
-  const int64_t cap = M >= 32 ? kMaxGrid : 1024;
+// slower). Their LLR-only calls write no partial sums.
+static int vec_grid(int64_t N, int M = 0, bool llr_only = false) {
+  const int64_t cap = M >= 32 ? kMaxGrid : (llr_only ? 2048 : 1024);
   const int64_t g = (N + kBlock - 1) / kBlock;
   return (int)(g < cap ? g : cap);
 }
@@ -384,7 +385,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   const size_t tsz = fp64 ? sizeof(double) : sizeof(float);
   // matrix-core tiles hold 16 or 32 points; smaller sets run the FP32 vector kernel
   const bool mfma = (prec == AIR_FP16X3 || prec == AIR_BF16X3) && c->M >= 16;
-  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M);
+  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M, !tx);
   const VecFn vfn = fp64 ? kVecF64[c->D] : kVecF32[c->D];
   const MfmaFn mfn = prec == AIR_BF16X3 ? kMfmaBF16[c->D] : kMfmaF16[c->D];
   const void* rec = prec == AIR_BF16X3 ? (const void*)c->rec_bf16 : (const void*)c->rec_f16;
@@ -401,11 +402,12 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   a.m = c->m;
   a.D = c->D;
   a.sweep = sweep;
-  // the FP32 vector kernel's exact form (AIR_FP32, and the matrix-core
-  // precisions on sets of fewer than 16 points) also has a second tier
-  const bool vec_t2 = !mfma && !fp64 && !maxlog;
+  // the vector kernels' exact forms of at most 16 points finish every item in
+  // one kernel; the FP32 form of more points also has a second tier
+  const bool small = !mfma && !maxlog && c->M <= 16;
+  const bool vec_t2 = !mfma && !fp64 && !maxlog && !small;
   int snr_per_launch = kMaxSnrPerLaunch;
-  if (mfma || vec_t2) {
+  if (mfma || (!fp64 && !maxlog)) {
     // per (SNR point, wave) a run of list slots, one per sample tile the wave
     // owns (matrix cores: pairs of tiles dealt out to the waves; vector
     // kernel: two tiles per wave and round, every slot written)
@@ -417,7 +419,9 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
     // tile indices, sample indices (with the padding of the last tile pair)
     // and per-SNR sample counts of the two tiers are 32-bit
     if (N > ((int64_t)1 << 32) - 128) return fail(ctx, AIR_E_UNSUPPORTED, "N too large for one call");
-    if (scratch) {
+    if (small && !scratch) {
+      // no lists
+    } else if (scratch) {
       // per SNR point of a launch: list slots (8 bytes), flagged counts per
       // wave (4) and 32 gathered sample indices per slot (4 each); three
       // parts, each starting on a 256-byte boundary
@@ -454,9 +458,13 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   a.err = &ctx->call->err;
   a.recomputed = &ctx->call->recomputed;
   a.exact = &ctx->call->exact;
+  // an LLR-only call of the small sets ends with its one kernel (no error to
+  // fold, no sums to reduce)
+  const bool one_kernel = small && !tx;
   for (int s0 = 0; s0 < S; s0 += snr_per_launch) {
     const int ns = (S - s0 < snr_per_launch) ? S - s0 : snr_per_launch;
     a.S = ns;
+    a.s_per = (ns + snr_slices(grid, ns) - 1) / snr_slices(grid, ns);
     fill_snr(a.snr, c, snr_db + s0, ns, aux);
     a.llr = llr ? (void*)((char*)llr + (size_t)s0 * N * c->m * tsz) : nullptr;
     // timed: the demapping kernel's dispatch itself sets the two events; they
@@ -477,12 +485,13 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
       lt.stop = ctx->ev[ctx->ev_used + 1];
       ctx->ev_used += 2;
     }
-    e = mfma ? mfn(a, rec, grid, lt, maxlog ? 2 : 0) : vfn(a, grid, lt, maxlog, 0);
+    e = mfma ? mfn(a, rec, grid, lt, maxlog ? 2 : 0) : vfn(a, grid, lt, maxlog, 0, one_kernel ? next : nullptr);
     if (e != hipSuccess) return hip_fail(ctx, e, "demapping kernel launch");
+    if (one_kernel) continue;
     const bool tier2 = (mfma && !maxlog) || vec_t2;
     if (tier2) {
       const Launch l2{ctx->stream, nullptr, nullptr};
-      e = mfma ? mfn(a, rec, grid, l2, 1) : vfn(a, grid, l2, false, 1);
+      e = mfma ? mfn(a, rec, grid, l2, 1) : vfn(a, grid, l2, false, 1, nullptr);
       if (e != hipSuccess) return hip_fail(ctx, e, "second-tier launch");
     }
     hipLaunchKernelGGL(finish_kernel, dim3(ns), dim3(256), 0, ctx->stream, ctx->partials,

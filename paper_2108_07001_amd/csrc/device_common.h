@@ -53,6 +53,17 @@ struct CallWords {
   unsigned long long exact;        // of those, items that needed the exact path
 };
 
+// Runs of SNR points a first-tier launch is cut into (gridDim.y), for a grid
+// of gx blocks over the samples: few samples leave most of the chip idle while
+// their waves walk all S points, so the points are dealt out until ~2048 blocks
+// exist. 1e4 samples, 41 points, with and without: 8-D/2048 964 -> 253 us, 4-D/256
+// 239 -> 71 us, 8-PSK^2 126 -> 46 us; 3e5 samples, 11 points: unchanged to 4 %
+// faster.
+inline int snr_slices(int gx, int S) {
+  const int n = 2048 / (gx > 0 ? gx : 1);
+  return n < 1 ? 1 : (n < S ? n : S);
+}
+
 // Zeroes the words of the next call (one thread).
 __device__ inline void clear_call_words(CallWords* next) {
   if (next) {
@@ -85,6 +96,7 @@ struct DemapArgs {
   int64_t N;
   int64_t llr_stride_s;             // elements between consecutive SNR planes of llr
   int M, m, D, S;
+  int s_per;                        // SNR points per block (blockIdx.y: a run of them)
   int sweep;                        // 1: y = x_t + sigma_s z from `in`
   // second tier (matrix-core forms and the FP32 vector kernel)
   unsigned long long* t2_list;      // [S][waves][tpw]: sample tile (32 bits) | lane mask (32)
@@ -158,8 +170,11 @@ __device__ __forceinline__ T sqdist(const T (&y)[D], const T* __restrict__ x) {
 // the difference a_j - a_r = -c (|y-x_j|^2 - |y-x_r|^2) is formed as
 // -c sum_d (x_r - x_j)_d (2 y - x_r - x_j)_d, which keeps its relative
 // accuracy even when y is far from every point (|a_j| huge, difference not).
-// Out of line and reloading the received point, so that the fast path's
-// registers stay untouched.
+// In line, with rolled loops and the sums copied to memory for them in the
+// branch that needs them: a call makes the kernel keep everything that lives
+// across it in every other block of eight registers (FP64, 16 points in 2-D: 185
+// registers with calls, 117 without), and a loop over a run-time number of
+// sums outside the branch put every item's sums into scratch memory.
 
 template <typename T, int D>
 __device__ __forceinline__ void reload_point(const T* __restrict__ in, int sweep,
@@ -186,13 +201,10 @@ __device__ __forceinline__ T rel_metric(const T (&y)[D], const T* __restrict__ x
 
 // Index (label order) of the point nearest to the received point; ties to the lowest.
 template <typename T, int D>
-__device__ __noinline__ int slow_nearest(const T* __restrict__ in, int sweep, const T* __restrict__ xl,
-                                         int M, T sigma, int64_t n, int tl) {
-  T y[D];
-  reload_point<T, D>(in, sweep, xl, sigma, n, tl, y);
+__device__ __forceinline__ int slow_nearest(const T (&y)[D], const T* __restrict__ xl, int M) {
   int best = 0;
   T bd = sqdist<T, D>(y, xl);
-#pragma unroll 4
+#pragma unroll sizeof(T) == 8 ? 2 : 4
   for (int j = 1; j < M; ++j) {
     T d2 = sqdist<T, D>(y, xl + (int64_t)j * D);
     if (d2 < bd) { bd = d2; best = j; }
@@ -200,28 +212,23 @@ __device__ __noinline__ int slow_nearest(const T* __restrict__ in, int sweep, co
   return best;
 }
 
-// log2 sum_{j in selection} 2^(a_j - a_r): bit side (k, b), all points (k = -1);
-// or a_t - a_r itself (k = -2).
+// log2 sum_{j in selection} 2^(a_j - a_r): bit side (k, b), or all points (k = -1).
 template <typename T, int D>
-__device__ __noinline__ T slow_rel(const T* __restrict__ in, int sweep, const T* __restrict__ xl,
-                                   int M, T sigma, T c, int64_t n, int tl, int r, int k, int b) {
-  T y[D];
-  reload_point<T, D>(in, sweep, xl, sigma, n, tl, y);
+__device__ __forceinline__ T slow_rel(const T (&y)[D], const T* __restrict__ xl, int M, T c, int r, int k, int b) {
   const T* xr = xl + (int64_t)r * D;
-  if (k == -2) return rel_metric<T, D>(y, xr, xl + (int64_t)tl * D, c);
   // the selection's labels: all of them, or those with bit k equal to b
   // (index i with b inserted at bit k)
   const int cnt = k >= 0 ? M >> 1 : M;
   const int lowmask = k >= 0 ? (1 << k) - 1 : 0;
   auto label = [&](int i) { return k >= 0 ? (((i & ~lowmask) << 1) | (b << k) | (i & lowmask)) : i; };
   T dmax = -__builtin_huge_val();
-#pragma unroll 4
+#pragma unroll sizeof(T) == 8 ? 2 : 4
   for (int i = 0; i < cnt; ++i) {
     T dj = rel_metric<T, D>(y, xr, xl + (int64_t)label(i) * D, c);
     dmax = dj > dmax ? dj : dmax;
   }
   T sum = 0;
-#pragma unroll 4
+#pragma unroll sizeof(T) == 8 ? 2 : 4
   for (int i = 0; i < cnt; ++i)
     sum += Real<T>::exp2(rel_metric<T, D>(y, xr, xl + (int64_t)label(i) * D, c) - dmax);
   return dmax + Real<T>::log2(sum);
@@ -270,6 +277,52 @@ __device__ __forceinline__ void finish_fast(int m, int tl, T total, const T (&si
   }
 }
 
+// The two outputs of an item beside its LLRs.
+template <typename T>
+struct ItemUV {
+  T u, v;
+};
+
+// Outputs of an item with starved entries: those are recomputed relative to
+// the nearest point r. If the total itself is starved, every entry is
+// recomputed and all stay relative to a_r (a side need not be below the total
+// bit for bit: the two are summed in different orders); otherwise the
+// recomputed sides are put back in the fast path's units by adding K + a_r,
+// which is then small. mem: the sums, replaced by their logarithms.
+template <typename T, int D>
+__device__ __forceinline__ ItemUV<T> finish_exact(const ExactArgs<T>& a, int64_t n, int tl, T total, T* mem,
+                                                  T arg_t, T* llr_out) {
+  const int m = a.m;
+  const T thr = Real<T>::starve(m);
+  T y[D];
+  reload_point<T, D>(a.in, a.sweep, a.xl, a.sigma, n, tl, y);
+  const int r = slow_nearest<T, D>(y, a.xl, a.M);
+  const bool total_slow = !(total >= thr);
+  const T base = total_slow ? T(0) : Real<T>::shift(m) - a.c * sqdist<T, D>(y, a.xl + (int64_t)r * D);
+  const uint32_t redo = exact_entries<T>(total, mem, m, thr);
+  T lam_tot = 0;
+  // entry -1: the total
+#pragma unroll 1
+  for (int i = -1; i < 2 * m; ++i) {
+    const bool slow = i < 0 ? total_slow : ((redo >> i) & 1u) != 0u;
+    const T lam = slow ? base + slow_rel<T, D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1)
+                       : Real<T>::log2(i < 0 ? total : mem[i]);
+    if (i < 0) lam_tot = lam;
+    else mem[i] = lam;
+  }
+  T acc = 0;
+#pragma unroll 1
+  for (int k = 0; k < m; ++k) {
+    if (llr_out) llr_out[k] = Real<T>::ln2() * (mem[2 * k] - mem[2 * k + 1]);
+    acc += lam_tot - mem[2 * k + ((tl >> k) & 1)];
+  }
+  T u = 0;
+  if (tl >= 0)
+    u = total_slow ? lam_tot - rel_metric<T, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)tl * D, a.c)
+                   : lam_tot - Real<T>::log2(Real<T>::exp2(arg_t));
+  return ItemUV<T>{u, acc};
+}
+
 // Outputs of one (sample, SNR) item from its fast-path sums, as finish_fast,
 // with the entries below the starvation bound recomputed exactly; the return
 // value says whether that happened (the caller counts such items).
@@ -279,59 +332,21 @@ __device__ __forceinline__ bool finish_item(const ExactArgs<T>& a, int64_t n, in
                                             T* llr_out, T& u, T& v) {
   const int m = a.m;
   const T thr = Real<T>::starve(m);
-  T lam[2 * kMaxBits];
-  T lam_tot;
   bool slow = !(total >= thr);
-  lam_tot = Real<T>::log2(total);
 #pragma unroll
-  for (int i = 0; i < 2 * kMaxBits; ++i) {
-    if (i < 2 * m) {
-      slow |= !(side[i] >= thr);
-      lam[i] = Real<T>::log2(side[i]);
+  for (int i = 0; i < 2 * kMaxBits; ++i)
+    if (i < 2 * m) slow |= !(side[i] >= thr);
+  if (!slow) {
+    finish_fast<T>(m, tl, total, side, arg_t, llr_out, u, v);
+  } else {
+    T mem[2 * kMaxBits];
+#pragma unroll
+    for (int i = 0; i < 2 * kMaxBits; ++i) mem[i] = side[i];
+    const ItemUV<T> r = finish_exact<T, D>(a, n, tl, total, mem, arg_t, llr_out);
+    if (tl >= 0) {
+      u = r.u;
+      v = r.v;
     }
-  }
-  bool total_slow = false;
-  T delta_t = 0;
-  if (slow) {
-    // Starved entries are recomputed relative to the nearest point r. If the
-    // total itself is starved, every entry is recomputed and all stay
-    // relative to a_r (a side need not be below the total bit for bit: the
-    // two are summed in different orders); otherwise the recomputed sides are
-    // put back in the fast path's units by adding K + a_r, which is then small.
-    const T* in = a.in;
-    const T* xl = a.xl;
-    const T sigma = a.sigma, c = a.c;
-    const int r = slow_nearest<T, D>(in, a.sweep, xl, a.M, sigma, n, tl);
-    total_slow = !(total >= thr);
-    T base = 0;
-    if (total_slow) {
-      lam_tot = slow_rel<T, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, -1, 0);
-      if (tl >= 0) delta_t = slow_rel<T, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, -2, 0);
-    } else {
-      T y[D];
-      reload_point<T, D>(in, a.sweep, xl, sigma, n, tl, y);
-      base = Real<T>::shift(m) - c * sqdist<T, D>(y, xl + (int64_t)r * D);
-    }
-    const uint32_t redo = exact_entries<T>(total, side, m, thr);
-#pragma unroll
-    for (int i = 0; i < 2 * kMaxBits; ++i)
-      if (i < 2 * m && ((redo >> i) & 1u))
-        lam[i] = base + slow_rel<T, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, i >> 1, i & 1);
-  }
-  if (llr_out) {
-#pragma unroll
-    for (int k = 0; k < kMaxBits; ++k)
-      if (k < m) llr_out[k] = Real<T>::ln2() * (lam[2 * k] - lam[2 * k + 1]);
-  }
-  if (tl >= 0) {
-    // log2 of the very term that entered the sum (not arg_t itself): u >= 0
-    // then holds exactly, whatever the rounding of exp2 and log2.
-    u = total_slow ? lam_tot - delta_t : lam_tot - Real<T>::log2(Real<T>::exp2(arg_t));
-    T acc = 0;
-#pragma unroll
-    for (int k = 0; k < kMaxBits; ++k)
-      if (k < m) acc += lam_tot - (((tl >> k) & 1) ? lam[2 * k + 1] : lam[2 * k]);
-    v = acc;
   }
   return slow;
 }
@@ -359,7 +374,7 @@ __device__ __forceinline__ double log2_wide(double x) {
 }
 
 // Outputs of one FP32-family item from sums in the FP64 frame 2^(a + K64)
-// (the matrix-core path's second tier). Entries below thr64 are recomputed
+// (the second tiers), this lane's own. Entries below thr64 are recomputed
 // exactly relative to the nearest point r and put back in the frame by
 // adding K64 + a_r; if the total itself is below thr64 every entry is
 // recomputed and all stay relative to a_r. lt_t is log2 of the transmitted
@@ -367,48 +382,39 @@ __device__ __forceinline__ double log2_wide(double x) {
 // recomputed). Only the starved entries cost a pass over the constellation.
 // The caller counts the item (it is one of the second tier's items).
 template <int D>
-__device__ __forceinline__ void finish_item_frame64(const ExactArgs<float>& a, int64_t n, int tl,
-                                                    double total, const double (&side)[2 * kMaxBits],
-                                                    double thr64, int K64, double lt_t,
-                                                    float* llr_out, float& u, float& v) {
+__device__ __forceinline__ void finish_item_frame64(const ExactArgs<float>& a, int64_t n, int tl, double total,
+                                                    const double (&side)[2 * kMaxBits], double thr64, int K64,
+                                                    double lt_t, float* llr_out, float& u, float& v) {
   const int m = a.m;
-  const float* in = a.in;
-  const float* xl = a.xl;
-  const float sigma = a.sigma, c = a.c;
-  const int r = slow_nearest<float, D>(in, a.sweep, xl, a.M, sigma, n, tl);
+  float y[D];
+  reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, n, tl, y);
+  const int r = slow_nearest<float, D>(y, a.xl, a.M);
   const bool total_slow = !(total >= thr64);
-  double lam[2 * kMaxBits];
-  double lam_tot, base = 0.0, delta_t = 0.0;
-  if (total_slow) {
-    lam_tot = (double)slow_rel<float, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, -1, 0);
-    if (tl >= 0) delta_t = (double)slow_rel<float, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, -2, 0);
-  } else {
-    float y[D];
-    reload_point<float, D>(in, a.sweep, xl, sigma, n, tl, y);
-    base = (double)K64 - (double)c * (double)sqdist<float, D>(y, xl + (int64_t)r * D);
-    lam_tot = log2_wide(total);
-  }
+  const double base =
+      total_slow ? 0.0 : (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
   const uint32_t redo = exact_entries<double>(total, side, m, thr64);
-#pragma unroll
-  for (int i = 0; i < 2 * kMaxBits; ++i) {
-    if (i < 2 * m) {
-      if ((redo >> i) & 1u)
-        lam[i] = base + (double)slow_rel<float, D>(in, a.sweep, xl, a.M, sigma, c, n, tl, r, i >> 1, i & 1);
-      else
-        lam[i] = log2_wide(side[i]);
+  double lam_tot = log2_wide(total);
+  double mem[2 * kMaxBits];      // logarithms of the recomputed entries; entry -1: the total
+#pragma unroll 1
+  for (int i = total_slow ? -1 : 0; i < 2 * m; ++i)
+    if (i < 0 || ((redo >> i) & 1u)) {
+      const double lam = base + (double)slow_rel<float, D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1);
+      if (i < 0) lam_tot = lam;
+      else mem[i] = lam;
     }
-  }
-  if (llr_out) {
+  double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < kMaxBits; ++k)
-      if (k < m) llr_out[k] = (float)(0.6931471805599453094 * (lam[2 * k] - lam[2 * k + 1]));
-  }
+  for (int k = 0; k < kMaxBits; ++k)
+    if (k < m) {
+      const double l0 = ((redo >> (2 * k)) & 1u) ? mem[2 * k] : log2_wide(side[2 * k]);
+      const double l1 = ((redo >> (2 * k + 1)) & 1u) ? mem[2 * k + 1] : log2_wide(side[2 * k + 1]);
+      if (llr_out) llr_out[k] = (float)(0.6931471805599453094 * (l0 - l1));
+      acc += lam_tot - (((tl >> k) & 1) ? l1 : l0);
+    }
   if (tl >= 0) {
-    u = (float)(total_slow ? lam_tot - delta_t : lam_tot - lt_t);
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < kMaxBits; ++k)
-      if (k < m) acc += lam_tot - (((tl >> k) & 1) ? lam[2 * k + 1] : lam[2 * k]);
+    const double delta_t =
+        total_slow ? (double)rel_metric<float, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)tl * D, a.c) : lt_t;
+    u = (float)(lam_tot - delta_t);
     v = (float)acc;
   }
 }
@@ -430,14 +436,12 @@ __device__ __forceinline__ double wave_sum(double x) {
 // 1.06 ms. Same metric and reference point as the per-lane form above; the
 // sums are taken per lane and then across the lanes.
 
-// Index of the point nearest to received point n (n, tl uniform); ties to the lowest.
+// Index of the point nearest to y (uniform); ties to the lowest.
 template <int D>
-__device__ __noinline__ int wave_nearest(const float* __restrict__ in, int sweep, const float* __restrict__ xl,
-                                         int M, float sigma, int64_t n, int tl) {
-  float y[D];
-  reload_point<float, D>(in, sweep, xl, sigma, n, tl, y);
+__device__ __forceinline__ int wave_nearest(const float (&y)[D], const float* __restrict__ xl, int M) {
   int best = 0;
   float bd = __builtin_inff();
+#pragma unroll 2
   for (int j = threadIdx.x & 63; j < M; j += 64) {
     const float d2 = sqdist<float, D>(y, xl + (int64_t)j * D);
     if (d2 < bd) { bd = d2; best = j; }
@@ -451,20 +455,17 @@ __device__ __noinline__ int wave_nearest(const float* __restrict__ in, int sweep
   return __builtin_amdgcn_readfirstlane(best);
 }
 
-// As slow_rel, for uniform n, tl, r, k, b: log2 sum over the selection of
-// 2^(a_j - a_r), or a_t - a_r itself (k = -2).
+// As slow_rel, for uniform y, r, k, b.
 template <int D>
-__device__ __noinline__ float wave_rel(const float* __restrict__ in, int sweep, const float* __restrict__ xl, int M,
-                                       float sigma, float c, int64_t n, int tl, int r, int k, int b) {
-  float y[D];
-  reload_point<float, D>(in, sweep, xl, sigma, n, tl, y);
+__device__ __forceinline__ float wave_rel(const float (&y)[D], const float* __restrict__ xl, int M, float c, int r,
+                                          int k, int b) {
   const float* xr = xl + (int64_t)r * D;
-  if (k == -2) return rel_metric<float, D>(y, xr, xl + (int64_t)tl * D, c);
   const int cnt = k >= 0 ? M >> 1 : M;
   const int lowmask = k >= 0 ? (1 << k) - 1 : 0;
   auto label = [&](int i) { return k >= 0 ? (((i & ~lowmask) << 1) | (b << k) | (i & lowmask)) : i; };
   const int lane = threadIdx.x & 63;
   float dmax = -__builtin_inff();
+#pragma unroll 2
   for (int i = lane; i < cnt; i += 64) {
     const float dj = rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c);
     dmax = dj > dmax ? dj : dmax;
@@ -475,6 +476,7 @@ __device__ __noinline__ float wave_rel(const float* __restrict__ in, int sweep, 
     dmax = o > dmax ? o : dmax;
   }
   float sum = 0.0f;
+#pragma unroll 2
   for (int i = lane; i < cnt; i += 64)
     sum += Real<float>::exp2(rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c) - dmax);
 #pragma unroll
@@ -483,31 +485,28 @@ __device__ __noinline__ float wave_rel(const float* __restrict__ in, int sweep, 
 }
 
 // Outputs of the lanes' FP32-family items (`mine`: this lane holds one) from
-// sums in the FP64 frame 2^(a + K64) (the second tiers); called by all lanes
-// of a wave together. Entries below thr64 are recomputed exactly relative to
-// the nearest point r and put back in the frame by adding K64 + a_r; if the
-// total itself is below thr64 every entry is recomputed and all stay relative
-// to a_r. lt_t is log2 of the transmitted point's own term in the frame (used
-// when tl >= 0 and the total is not recomputed). Only the starved entries cost
-// a pass over the constellation. The caller counts the items.
+// sums in the FP64 frame 2^(a + K64), as finish_item_frame64; called by all
+// lanes of a wave together.
 template <int D>
 __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
-                                                     double total, double (&side)[2 * kMaxBits], double thr64,
-                                                     int K64, double lt_t, float* llr_out, float& u, float& v) {
+                                                     double total, const double (&side)[2 * kMaxBits],
+                                                     double thr64, int K64, double lt_t, float* llr_out, float& u,
+                                                     float& v) {
   unsigned long long todo = __ballot(mine);
   if (!todo) return;
   // A pass costs the lanes' own form M points however many of them hold an
-  // item, and this one M / 64 points and the call, the sample's loads and the
-  // exchanges per item, ~480 instructions or as many points as those take at
-  // ~3 D + 8 each (D = 1, M = 2048, 32 items per wave: 27.2 against 23.0 ms for
-  // the lanes' form, so the line there lies near 27 items).
-  constexpr int kCall = 480 / (3 * D + 8);
-  if (__builtin_popcountll(todo) * ((a.M >> 6) + kCall) >= a.M) {
+  // item (and it takes the passes that any of them needs), and this one M / 64
+  // points and the exchanges per item: 3 points' worth. 1e6 samples of 4-D sets at
+  // high SNR, start / all lanes' form / this line: 64 points at 30 dB 1.19 /
+  // 1.53 / 0.71 ms, 128 at 30 dB 1.93 / 2.58 / 0.55 ms; 16 points at 28 dB 0.34 /
+  // 0.33 / 0.34 (0.56 with the line at 1 point).
+  if (__builtin_popcountll(todo) * ((a.M >> 6) + 3) >= a.M) {
     if (mine) finish_item_frame64<D>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
     return;
   }
   const int m = a.m;
   const int lane = threadIdx.x & 63;
+  double mem[2 * kMaxBits];      // logarithms of the recomputed entries
   const uint32_t redo = mine ? exact_entries<double>(total, side, m, thr64) : 0u;
   const bool total_slow = !(total >= thr64);
   double lam_tot = log2_wide(total), delta_t = 0.0;
@@ -519,29 +518,25 @@ __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, 
     const int ts = __builtin_amdgcn_readlane(tl, src);
     uint32_t rs = __builtin_amdgcn_readlane(redo, src);
     const bool all = __builtin_amdgcn_readlane(total_slow ? 1 : 0, src) != 0;
-    const int r = wave_nearest<D>(a.in, a.sweep, a.xl, a.M, a.sigma, ns, ts);
-    double base = 0.0;
-    if (all) {
-      const double lt = (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, -1, 0);
-      const double dt =
-          ts >= 0 ? (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, -2, 0) : 0.0;
-      if (lane == src) {
-        lam_tot = lt;
-        delta_t = dt;
-      }
-    } else {
-      float y[D];
-      reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, ns, ts, y);
-      base = (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
+    float y[D];
+    reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, ns, ts, y);
+    const int r = wave_nearest<D>(y, a.xl, a.M);
+    const double base =
+        all ? 0.0 : (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
+    if (all && ts >= 0) {
+      const double dt = (double)rel_metric<float, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)ts * D, a.c);
+      if (lane == src) delta_t = dt;
     }
-    while (rs) {
-      const int i = __builtin_ctz(rs);
-      rs &= rs - 1u;
-      const double lam =
-          base + (double)wave_rel<D>(a.in, a.sweep, a.xl, a.M, a.sigma, a.c, ns, ts, r, i >> 1, i & 1);
-      // (a chain of selects: no index into the lane's array)
-#pragma unroll
-      for (int e = 0; e < 2 * kMaxBits; ++e) side[e] = (e == i && lane == src) ? lam : side[e];
+    // the total (entry -1) if it is starved, then the starved sides
+    int i = all ? -1 : __builtin_ctz(rs | 0x80000000u);
+    while (i < 2 * m) {
+      const double lam = base + (double)wave_rel<D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1);
+      if (lane == src) {
+        if (i < 0) lam_tot = lam;
+        else mem[i] = lam;
+      }
+      if (i >= 0) rs &= rs - 1u;
+      i = __builtin_ctz(rs | 0x80000000u);
     }
   }
   if (mine) {
@@ -549,9 +544,8 @@ __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, 
 #pragma unroll
     for (int k = 0; k < kMaxBits; ++k)
       if (k < m) {
-        // recomputed entries hold their logarithm, the others the sum
-        const double l0 = ((redo >> (2 * k)) & 1u) ? side[2 * k] : log2_wide(side[2 * k]);
-        const double l1 = ((redo >> (2 * k + 1)) & 1u) ? side[2 * k + 1] : log2_wide(side[2 * k + 1]);
+        const double l0 = ((redo >> (2 * k)) & 1u) ? mem[2 * k] : log2_wide(side[2 * k]);
+        const double l1 = ((redo >> (2 * k + 1)) & 1u) ? mem[2 * k + 1] : log2_wide(side[2 * k + 1]);
         if (llr_out) llr_out[k] = (float)(0.6931471805599453094 * (l0 - l1));
         acc += lam_tot - (((tl >> k) & 1) ? l1 : l0);
       }

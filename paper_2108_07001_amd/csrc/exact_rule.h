@@ -17,8 +17,11 @@ template <typename T>
 constexpr uint32_t exact_entries(T total, const T* side, int m, T thr) {
   const bool total_slow = !(total >= thr);
   uint32_t mask = 0;
-  for (int i = 0; i < 2 * m; ++i)
-    if (total_slow || !(side[i] >= thr)) mask |= 1u << i;
+  // (24 entries at most, 4096 points; unrolled, so that no index into the
+  // caller's sums keeps them out of registers)
+#pragma unroll
+  for (int i = 0; i < 24; ++i)
+    if (i < 2 * m && (total_slow || !(side[i] >= thr))) mask |= 1u << i;
   return mask;
 }
 

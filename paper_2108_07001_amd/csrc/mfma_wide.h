@@ -510,18 +510,20 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
   // where they fit into 256 with the rest
   constexpr bool PIPE = w_pipe<D, BF>(MB, ML);
   constexpr int NSET = D <= 12 ? 2 : 1;
-  extern __shared__ double acc_lds[];      // [waves][S][4], then the tables (TBL)
+  extern __shared__ double acc_lds[];      // [waves][s_per][4], then the tables (TBL)
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
   const int j = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wave
   const int waves = blockDim.x >> 6;
-  const int S = a.S;
+  // the block's SNR points s0 .. s1 - 1
+  const int s0 = blockIdx.y * a.s_per;
+  const int s1 = s0 + a.s_per < a.S ? s0 + a.s_per : a.S;
   Tables<BF> tb{a.lab, xl, rec};
   if (TBL) {
     const int M = a.M;
     char* lds = reinterpret_cast<char*>(acc_lds);
-    const int o_lab = waves * S * 4 * (int)sizeof(double);
+    const int o_lab = waves * a.s_per * 4 * (int)sizeof(double);
     const int o_xl = o_lab + M * 4;
     const int o_rec = (o_xl + M * D * 4 + 15) & ~15;
     uint32_t* l_lab = reinterpret_cast<uint32_t*>(lds + o_lab);
@@ -557,7 +559,7 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
   // (blocks are dealt to the 8 XCDs in turn), whose L2 still holds its
   // inputs from the previous SNR point.
   const QI rem = npairs % wstride;
-  for (int s = 0; s < S; ++s) {
+  for (int s = s0; s < s1; ++s) {
     double au = 0.0, av = 0.0, auu = 0.0, avv = 0.0;
     unsigned long long* slots = a.t2_list + ((int64_t)s * wstride + wgid) * a.t2_tpw;
     int nlisted = 0;
@@ -928,7 +930,7 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
     const double w0 = wave_sum(au), w1 = wave_sum(av);
     const double w2 = wave_sum(auu), w3 = wave_sum(avv);
     if (lane == 0) {
-      double* acc = acc_lds + ((int64_t)wave * S + s) * 4;
+      double* acc = acc_lds + (wave * a.s_per + (s - s0)) * 4;
       acc[0] = w0;
       acc[1] = w1;
       acc[2] = w2;
@@ -936,10 +938,10 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
+  for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
     double t = 0.0;
-    for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    a.partials[(int64_t)i * gridDim.x + blockIdx.x] = t;
+    for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
+    a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
   }
 }
 
@@ -948,21 +950,22 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
 template <int D, bool BF, bool ML>
 void launch_first_tier(const DemapArgs& a, const typename MfmaOp<BF>::vec* r, const float* x, int grid,
                        const Launch& l) {
-  const uint32_t acc = (uint32_t)(sizeof(double) * 4 * a.S * 4);
+  const uint32_t acc = (uint32_t)(sizeof(double) * 4 * a.s_per * 4);
+  const dim3 g(grid, (a.S + a.s_per - 1) / a.s_per);
   const int64_t tbytes = table_bytes(a.M, D, BF);
   const bool tbl = tbytes <= 40 * 1024;
   const uint32_t lds = acc + (uint32_t)tbytes;
   // the exact-size forms hold their tables in LDS (at most 12.5 KB for M = 64)
   if (a.M == 16)
-    launch_kernel(l, demap_mfma_w<D, BF, true, 4, ML>, dim3(grid), dim3(256), lds, a, r, x);
+    launch_kernel(l, demap_mfma_w<D, BF, true, 4, ML>, g, dim3(256), lds, a, r, x);
   else if (a.M == 32)
-    launch_kernel(l, demap_mfma_w<D, BF, true, 5, ML>, dim3(grid), dim3(256), lds, a, r, x);
+    launch_kernel(l, demap_mfma_w<D, BF, true, 5, ML>, g, dim3(256), lds, a, r, x);
   else if (a.M == 64)
-    launch_kernel(l, demap_mfma_w<D, BF, true, 6, ML>, dim3(grid), dim3(256), lds, a, r, x);
+    launch_kernel(l, demap_mfma_w<D, BF, true, 6, ML>, g, dim3(256), lds, a, r, x);
   else if (tbl)
-    launch_kernel(l, demap_mfma_w<D, BF, true, 0, ML>, dim3(grid), dim3(256), lds, a, r, x);
+    launch_kernel(l, demap_mfma_w<D, BF, true, 0, ML>, g, dim3(256), lds, a, r, x);
   else
-    launch_kernel(l, demap_mfma_w<D, BF, false, 0, ML>, dim3(grid), dim3(256), acc, a, r, x);
+    launch_kernel(l, demap_mfma_w<D, BF, false, 0, ML>, g, dim3(256), acc, a, r, x);
 }
 
 // One part of the matrix-core path for one (D, operand type). part 0: the

@@ -81,11 +81,14 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
   constexpr int NL = kMaxBits - LG;
   // FP32 exact form: starved items go to the second tier (demap_vec_t2)
   constexpr bool T2 = !ML && sizeof(T) == 4;
-  extern __shared__ double acc_lds[];  // [waves][S][4], then (T2) flagged counts [waves][S]
+  extern __shared__ double acc_lds[];  // [waves][s_per][4], then (T2) flagged counts [waves][s_per]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wave
   const int waves = blockDim.x >> 6;
-  const int S = a.S;
+  // the block's SNR points s0 .. s1 - 1
+  const int s0 = blockIdx.y * a.s_per;
+  const int s1 = s0 + a.s_per < a.S ? s0 + a.s_per : a.S;
+  const int S = a.s_per;
   unsigned int* nflag_lds = reinterpret_cast<unsigned int*>(acc_lds + waves * S * 4);
   for (int i = threadIdx.x; i < waves * S * 4; i += blockDim.x) acc_lds[i] = 0.0;
   if (T2)
@@ -110,13 +113,13 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
     if (valid && a.tx) {
       const uint32_t t = a.tx[n];
       if (t >= (uint32_t)M) {
-        atomicOr(a.err, 1);
+        if (s0 == 0) atomicOr(a.err, 1);
         tl = -2;
       } else {
         tl = (int)a.lab[t];
       }
     }
-    for (int s = 0; s < S; ++s) {
+    for (int s = s0; s < s1; ++s) {
       double su = 0.0, sv = 0.0;
       bool need2 = false;            // T2: a starved entry, finished by the second tier
       T* lout = (llr && valid) ? llr + (int64_t)s * a.llr_stride_s + n * m : nullptr;
@@ -250,13 +253,13 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
           unsigned long long* slot = a.t2_list + ((int64_t)s * wstride + wgid) * a.t2_tpw + 2 * r;
           slot[0] = ((bm & 0xffffffffull) << 32) | (unsigned long long)(uint32_t)tile;
           slot[1] = (bm & 0xffffffff00000000ull) | (unsigned long long)(uint32_t)(tile + 1);
-          nflag_lds[wave * S + s] += (unsigned int)__builtin_popcountll(bm);
+          nflag_lds[wave * S + s - s0] += (unsigned int)__builtin_popcountll(bm);
         }
       }
       const double w0 = wave_sum(su), w1 = wave_sum(sv);
       const double w2 = wave_sum(su * su), w3 = wave_sum(sv * sv);
       if (lane == 0) {
-        double* acc = acc_lds + ((int64_t)wave * S + s) * 4;
+        double* acc = acc_lds + (wave * S + s - s0) * 4;
         acc[0] += w0;
         acc[1] += w1;
         acc[2] += w2;
@@ -272,12 +275,267 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
     atomicAdd(a.exact, (unsigned long long)wslow);
   }
   if (T2)
-    for (int s = lane; s < S; s += 64) a.t2_nitem[(int64_t)s * wstride + wgid] = nflag_lds[wave * S + s];
+    for (int s = s0 + lane; s < s1; s += 64) a.t2_nitem[(int64_t)s * wstride + wgid] = nflag_lds[wave * S + s - s0];
   __syncthreads();
-  for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
+  for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    a.partials[(int64_t)i * gridDim.x + blockIdx.x] = t;
+    a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// First tier of the small sets (M = G <= 16 points) with the second tier's work
+// in the same kernel, and the FP64 form of those sets. Here a sample costs
+// little, so what surrounds it weighs: the listing, gathering and re-reading
+// of the flagged items by two more kernels, four wave sums per round and SNR
+// point, and for the LLR-only calls a reduction that nothing reads. So
+//  - the SNR points are outermost, and each lane keeps its four FP64 sums over
+//    its samples (one wave sum per SNR point);
+//  - FP32: the flagged samples of a wave are queued in LDS (sample, SNR point)
+//    and re-formed 64 at a time in the FP64 frame of demap_vec_t2, across
+//    rounds and SNR points, so that only the wave's last batch is partly empty;
+//    their sums are added per SNR point, in queue order;
+//  - calls without transmitted indices write no partial sums and need no
+//    reduction kernel (block (0, 0) zeroes the next call's words).
+// 8-QAM, 2^20 symbols at 18 dB (392170 flagged, LLRs): four kernels of 22 + 18 +
+// 41 + 4 us -> one of 30 us; a frame of 1000 16-QAM symbols 14.7 -> 7.4 us; FP64
+// PM-QPSK, 1e5 samples, 5 points 58 -> 38 us (there 16 exponentials and 9
+// logarithms of ~30 instructions each are most of it). Terms, sums and outputs
+// per item are those of demap_vec and demap_vec_t2.
+template <typename T, int D, int G>
+__global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, const T* __restrict__ xl,
+                                                          CallWords* next) {
+  constexpr int m = Log2G<G>::v;
+  constexpr bool F32 = sizeof(T) == 4;
+  extern __shared__ double acc_lds[];            // [waves][s_per][4]
+  __shared__ uint2 queue[F32 ? kBlock / 64 : 1][128];   // flagged (sample, SNR point), per wave
+  __shared__ unsigned int counts[2];             // items outside the first tier, of them exact
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wave
+  const int waves = blockDim.x >> 6;
+  const int s0 = blockIdx.y * a.s_per;
+  const int s1 = s0 + a.s_per < a.S ? s0 + a.s_per : a.S;
+  if (threadIdx.x < 2) counts[threadIdx.x] = 0u;
+  double* wacc = acc_lds + wave * a.s_per * 4;
+  for (int i = lane; i < a.s_per * 4; i += 64) wacc[i] = 0.0;
+  __syncthreads();
+  const T K = Real<T>::shift(m);
+  T* __restrict__ llr = static_cast<T*>(a.llr);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  unsigned int items = 0, exact = 0;             // wave-uniform (FP32), per lane (FP64)
+  int qn = 0;                                    // queued samples of this wave
+
+  // the first `cnt` queued samples (one per lane) in the FP64 frame
+  auto finish_queued = [&](int cnt) {
+    if constexpr (F32) {
+      constexpr int K64 = 1022 - m;
+      const int dK = K64 - (int)K;
+      const double thr64 = __builtin_ldexp(1.0, m - 1022 + 60);
+      auto val64 = [&](float x) -> double {
+        const float fr = __builtin_amdgcn_fractf(x);    // x - floor(x), in [0, 1)
+        const int ni = (int)__builtin_floorf(x);
+        return __builtin_ldexp((double)Real<float>::exp2(fr), ni + dK);
+      };
+      const bool has = lane < cnt;
+      const uint2 ent = queue[wave][lane];
+      const int s = has ? (int)ent.y : s0;
+      float u = 0.f, v = 0.f;
+      bool ex_lane = false;
+      int tl = -1;
+      if (has) {
+        const int64_t n = (int64_t)ent.x;
+        tl = a.tx ? (int)a.lab[a.tx[n]] : -1;
+        const float c = a.snr.cf[s];
+        float y[D];
+        load_point<float, D>(a, n, tl, a.snr.sigmaf[s], y);
+        double e[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) e[i] = val64(__builtin_fmaf(-c, sqdist<float, D>(y, xl + i * D), K));
+        const double total = tree_sum<double, G>(e);
+        double side[2 * kMaxBits];
+#pragma unroll
+        for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
+#pragma unroll
+        for (int k = 0; k < m; ++k) {
+          double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+          for (int i = 0; i < G; ++i) {
+            if ((i >> k) & 1) a1 += e[i];
+            else a0 += e[i];
+          }
+          side[2 * k] = a0;
+          side[2 * k + 1] = a1;
+        }
+        // log2 of the transmitted point's own term as it entered the sums
+        const double lt_t =
+            tl >= 0 ? log2_wide(val64(__builtin_fmaf(-c, sqdist<float, D>(y, xl + (int64_t)tl * D), K))) : 0.0;
+        double smin = total;
+#pragma unroll
+        for (int i = 0; i < 2 * m; ++i) smin = __builtin_fmin(smin, side[i]);
+        float* lout = llr ? llr + (int64_t)s * a.llr_stride_s + n * m : nullptr;
+        if (smin >= thr64) {
+          const double lt = log2_wide(total);
+          double vacc = 0.0;
+#pragma unroll
+          for (int k = 0; k < m; ++k) {
+            const double l0 = log2_wide(side[2 * k]), l1 = log2_wide(side[2 * k + 1]);
+            if (lout) lout[k] = (float)(0.6931471805599453094 * (l0 - l1));
+            vacc += lt - (((tl >> k) & 1) ? l1 : l0);
+          }
+          u = (float)(lt - lt_t);
+          v = (float)vacc;
+        } else {
+          // (at most 16 points: the lanes' own form of the exact path)
+          finish_item_frame64<D>(exact_args<float>(a, s), n, tl, total, side, thr64, K64, lt_t, lout, u, v);
+          ex_lane = true;
+        }
+      }
+      items += (unsigned int)cnt;
+      exact += (unsigned int)__builtin_popcountll(__ballot(ex_lane));
+      if (a.tx) {
+        // sums per SNR point, in queue order (the points do not decrease)
+        unsigned long long left = __ballot(has);
+        while (left) {
+          const int sc = __builtin_amdgcn_readlane(s, __builtin_ctzll(left));
+          const bool in = has && s == sc;
+          left &= ~__ballot(in);
+          const double du = in ? (double)u : 0.0, dv = in ? (double)v : 0.0;
+          const double w0 = wave_sum(du), w1 = wave_sum(dv);
+          const double w2 = wave_sum(du * du), w3 = wave_sum(dv * dv);
+          if (lane == 0) {
+            double* acc = wacc + (sc - s0) * 4;
+            acc[0] += w0;
+            acc[1] += w1;
+            acc[2] += w2;
+            acc[3] += w3;
+          }
+        }
+      }
+    }
+  };
+
+  for (int s = s0; s < s1; ++s) {
+    const T c = Real<T>::c(a.snr, s);
+    const T sigma = Real<T>::sigma(a.snr, s);
+    double au = 0.0, av = 0.0, auu = 0.0, avv = 0.0;
+    // (every lane of a wave takes the same number of rounds: the ballots and
+    // the queue need the whole wave)
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + wave * 64; b < a.N; b += stride) {
+      const int64_t n = b + lane;
+      const bool valid = n < a.N;
+      int tl = -1;  // label of the transmitted point; -2 marks an invalid index
+      if (valid && a.tx) {
+        const uint32_t t = a.tx[n];
+        if (t >= (uint32_t)G) {
+          if (s == 0) atomicOr(a.err, 1);
+          tl = -2;
+        } else {
+          tl = (int)a.lab[t];
+        }
+      }
+      T* lout = (llr && valid) ? llr + (int64_t)s * a.llr_stride_s + n * m : nullptr;
+      bool need2 = false;            // FP32: a starved entry, finished from the queue
+      if (valid && tl != -2) {
+        T y[D];
+        load_point<T, D>(a, n, tl, sigma, y);
+        T e[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) e[i] = Real<T>::exp2(Real<T>::fma(-c, sqdist<T, D>(y, xl + i * D), K));
+        const T total = tree_sum<T, G>(e);
+        T side[2 * kMaxBits];
+#pragma unroll
+        for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0;
+#pragma unroll
+        for (int k = 0; k < m; ++k) {
+          T a0 = 0, a1 = 0;
+#pragma unroll
+          for (int i = 0; i < G; ++i) {
+            if ((i >> k) & 1) a1 += e[i];
+            else a0 += e[i];
+          }
+          side[2 * k] = a0;
+          side[2 * k + 1] = a1;
+        }
+        T u = 0, v = 0, arg_t = 0;
+        if (tl >= 0) arg_t = Real<T>::fma(-c, sqdist<T, D>(y, xl + (int64_t)tl * D), K);
+        if constexpr (F32) {
+          // as in demap_vec: the smallest sum that the call uses decides
+          T smin = total;
+          if (llr) {
+#pragma unroll
+            for (int i = 0; i < 2 * m; ++i) smin = __builtin_fminf(smin, side[i]);
+          } else {
+#pragma unroll
+            for (int k = 0; k < m; ++k) smin = __builtin_fminf(smin, ((tl >> k) & 1) ? side[2 * k + 1] : side[2 * k]);
+          }
+          need2 = !(smin >= Real<T>::starve(m));
+          if (!need2) finish_fast<T>(m, tl, total, side, arg_t, lout, u, v);
+        } else {
+          exact += finish_item<T, D>(exact_args<T>(a, s), n, tl, total, side, arg_t, lout, u, v) ? 1u : 0u;
+        }
+        if (tl >= 0 && !need2) {
+          const double du = (double)u, dv = (double)v;
+          au += du;
+          av += dv;
+          auu = __builtin_fma(du, du, auu);
+          avv = __builtin_fma(dv, dv, avv);
+        }
+      } else if (lout) {
+        for (int k = 0; k < m; ++k) lout[k] = Real<T>::nan();
+      }
+      if constexpr (F32) {
+        const unsigned long long bm = __ballot(need2);
+        if (bm) {
+          // (one wave's queue: its own LDS operations are in order)
+          const int at = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(bm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bm, 0u));
+          if (need2) queue[wave][at] = make_uint2((uint32_t)n, (uint32_t)s);
+          qn += __builtin_popcountll(bm);
+          __builtin_amdgcn_wave_barrier();
+          if (qn >= 64) {
+            finish_queued(64);
+            __builtin_amdgcn_wave_barrier();
+            const uint2 rest = queue[wave][64 + lane];
+            __builtin_amdgcn_wave_barrier();
+            queue[wave][lane] = rest;
+            qn -= 64;
+          }
+        }
+      }
+    }
+    if (a.tx) {
+      const double w0 = wave_sum(au), w1 = wave_sum(av);
+      const double w2 = wave_sum(auu), w3 = wave_sum(avv);
+      if (lane == 0) {
+        double* acc = wacc + (s - s0) * 4;
+        acc[0] += w0;
+        acc[1] += w1;
+        acc[2] += w2;
+        acc[3] += w3;
+      }
+    }
+  }
+  if constexpr (F32) {
+    __builtin_amdgcn_wave_barrier();
+    if (qn > 0) finish_queued(qn);
+  } else {
+    exact = (unsigned int)wave_sum((double)exact);
+    items = exact;
+  }
+  if (lane == 0 && items) {
+    atomicAdd(&counts[0], items);
+    atomicAdd(&counts[1], exact);
+  }
+  __syncthreads();
+  if (a.tx)
+    for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
+      double t = 0.0;
+      for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
+      a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
+    }
+  if (threadIdx.x == 0) {
+    if (counts[0]) atomicAdd(a.recomputed, (unsigned long long)counts[0]);
+    if (counts[1]) atomicAdd(a.exact, (unsigned long long)counts[1]);
+    if (next && blockIdx.x == 0 && blockIdx.y == 0) clear_call_words(next);
   }
 }
 
@@ -483,40 +741,51 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
   }
 }
 
-// part 0: the first tier (exact or, with ml, max-log); part 1 (FP32 exact
-// form only): the gather of the first tier's lists and the second tier. The
-// events of `l` time part 0's kernel only.
+// part 0: the first tier (exact or, with ml, max-log); part 1 (FP32 exact form
+// of more than 16 points only): the gather of the first tier's lists and the
+// second tier. `next`: the next call's words for a launch that no reduction
+// follows, else null. The events of `l` time part 0's kernel only.
 template <typename T, int D, int G>
-hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml, int part) {
-  const uint32_t acc = (uint32_t)(sizeof(double) * (kBlock / 64) * a.S * 4);
-  if (part == 1) {
-    if (!a.t2_items || !a.t2_tot || !a.t2_partials) return hipErrorInvalidValue;
-    if constexpr (sizeof(T) == 4) {
-      launch_t2_collect(a, grid, l.stream);
-      hipLaunchKernelGGL((demap_vec_t2<D, G>), dim3(t2_grid(grid, a.M)), dim3(kBlock), acc, l.stream, a,
-                         static_cast<const float*>(a.xl));
-    }
+hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml, int part, CallWords* next) {
+  const uint32_t acc = (uint32_t)(sizeof(double) * (kBlock / 64) * a.s_per * 4);
+  const dim3 g(grid, (a.S + a.s_per - 1) / a.s_per);
+  if (ml) {
+    launch_kernel(l, demap_vec<T, D, G, true>, g, dim3(kBlock), acc, a, static_cast<const T*>(a.xl));
     return hipGetLastError();
   }
-  // the FP32 exact form lists its starved items: no launch without the lists
-  if (!ml && sizeof(T) == 4 && (!a.t2_list || !a.t2_nitem || a.t2_tpw < 1)) return hipErrorInvalidValue;
-  if (ml)
-    launch_kernel(l, demap_vec<T, D, G, true>, dim3(grid), dim3(kBlock), acc, a, static_cast<const T*>(a.xl));
-  else
-    launch_kernel(l, demap_vec<T, D, G, false>, dim3(grid), dim3(kBlock),
-                  acc + (sizeof(T) == 4 ? (uint32_t)(sizeof(unsigned int) * (kBlock / 64) * a.S) : 0u), a,
+  if (a.M <= 16) {
+    if (a.M != G || part != 0) return hipErrorInvalidValue;
+    launch_kernel(l, demap_vec_small<T, D, G>, g, dim3(kBlock), acc, a, static_cast<const T*>(a.xl), next);
+    return hipGetLastError();
+  }
+  if constexpr (G == 16) {
+    if (part == 1) {
+      if (!a.t2_items || !a.t2_tot || !a.t2_partials) return hipErrorInvalidValue;
+      if constexpr (sizeof(T) == 4) {
+        launch_t2_collect(a, grid, l.stream);
+        hipLaunchKernelGGL((demap_vec_t2<D, G>), dim3(t2_grid(grid, a.M)), dim3(kBlock),
+                           (uint32_t)(sizeof(double) * (kBlock / 64) * a.S * 4), l.stream, a,
+                           static_cast<const float*>(a.xl));
+      }
+      return hipGetLastError();
+    }
+    // the FP32 exact form lists its starved items: no launch without the lists
+    if (sizeof(T) == 4 && (!a.t2_list || !a.t2_nitem || a.t2_tpw < 1)) return hipErrorInvalidValue;
+    launch_kernel(l, demap_vec<T, D, G, false>, g, dim3(kBlock),
+                  acc + (sizeof(T) == 4 ? (uint32_t)(sizeof(unsigned int) * (kBlock / 64) * a.s_per) : 0u), a,
                   static_cast<const T*>(a.xl));
+  }
   return hipGetLastError();
 }
 
 // ml: the max-log form.
 template <typename T, int D>
-hipError_t launch_vec_td(const DemapArgs& a, int grid, const Launch& l, bool ml, int part) {
+hipError_t launch_vec_td(const DemapArgs& a, int grid, const Launch& l, bool ml, int part, CallWords* next) {
   switch (a.M >= 16 ? 16 : a.M) {
-    case 2: return launch_vec_one<T, D, 2>(a, grid, l, ml, part);
-    case 4: return launch_vec_one<T, D, 4>(a, grid, l, ml, part);
-    case 8: return launch_vec_one<T, D, 8>(a, grid, l, ml, part);
-    default: return launch_vec_one<T, D, 16>(a, grid, l, ml, part);
+    case 2: return launch_vec_one<T, D, 2>(a, grid, l, ml, part, next);
+    case 4: return launch_vec_one<T, D, 4>(a, grid, l, ml, part, next);
+    case 8: return launch_vec_one<T, D, 8>(a, grid, l, ml, part, next);
+    default: return launch_vec_one<T, D, 16>(a, grid, l, ml, part, next);
   }
 }
 

@@ -231,3 +231,57 @@ def test_fp32_second_tier_counts_and_results_repeat(ctx):
     ref = oracle.sweep(hi.X, hi.labels, hi.tx, hi.z, hi.snr_db)
     assert_stats(a[0], ref["stats"])
     assert_llr(a[1], ref["llr"])
+
+
+@pytest.mark.parametrize("M,D", [(2, 1), (4, 2), (8, 3), (16, 2), (16, 16)])
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 1000, 70001])
+def test_small_sets_one_kernel(ctx, M, D, N):
+    # sets of at most 16 points: items beyond the FP32 frame are queued per wave
+    # and finished 64 at a time across rounds and SNR points (none, a few and
+    # all of them flagged here, the last batch of any size); an LLR-only call,
+    # one kernel with no reduction, gives the same LLRs
+    X, lab = inputs.random_constellation(17 * M + D, M, D)
+    tx, z = inputs.random_block(N + 3 * M, M, N, D)
+    snr = np.array([3.0, 14.0, 19.0, 24.0, 29.0])
+    c = ctx.const(X, lab)
+    st, L = ctx.sweep(c, tx_dev(tx), to_dev(z), snr, prec="fp32", llr=True)
+    ctx.sync()
+    st, L = st.cpu().numpy(), L.cpu().numpy()
+    ref = oracle.sweep(X, lab, tx, z, snr)
+    assert_stats(st, ref["stats"], se_rel=2e-2)
+    assert_llr(L, ref["llr"])
+    st64, L64 = ctx.sweep(c, tx_dev(tx), to_dev(z.astype(np.float64)), snr, prec="fp64", llr=True)
+    ctx.sync()
+    assert_stats(st64.cpu().numpy(), ref["stats"], tol=1e-11, se_rel=1e-6)
+    assert_llr(L64.cpu().numpy(), ref["llr"], 1e-11)
+    for s in (1, 3):
+        Y = (np.float32(math.sqrt(oracle.sigma2(X, snr[s]))) * z + X[tx]).astype(np.float32)
+        La = ctx.llr(c, to_dev(Y), snr[s], prec="fp32")
+        na = (ctx.last_recomputed(), ctx.last_exact())
+        sb, Lb = ctx.mi_gmi(c, to_dev(Y), tx_dev(tx), snr[s], prec="fp32", llr=True)
+        ctx.sync()
+        assert torch.equal(La, Lb) and na == (ctx.last_recomputed(), ctx.last_exact())
+    c.close()
+
+
+@pytest.mark.parametrize("M,D,prec", [(8, 2, "fp32"), (64, 4, "fp32"), (16, 4, "fp64"), (64, 4, "fp64"),
+                                      (16, 2, "fp16x3"), (64, 4, "bf16x3"), (256, 4, "fp16x3")])
+@pytest.mark.parametrize("N,S", [(1, 64), (300, 41), (3000, 70), (90000, 7)])
+def test_snr_points_dealt_out_to_blocks(ctx, M, D, prec, N, S):
+    # short blocks of samples: each block takes a run of the SNR points (one
+    # point, several, a shorter last run); every point equals its own call
+    X, lab = inputs.random_constellation(M + S, M, D)
+    tx, z = inputs.random_block(N, M, N, D, f64=prec == "fp64")
+    snr = np.linspace(-1.0, 23.0, S)
+    c = ctx.const(X, lab)
+    st, L = ctx.sweep(c, tx_dev(tx), to_dev(z), snr, prec=prec, llr=True)
+    ml, Lm = ctx.sweep_maxlog(c, tx_dev(tx), to_dev(z), snr, prec=prec, llr=True)
+    for s in sorted({0, 1, S // 2, S - 1}):
+        st1, L1 = ctx.sweep(c, tx_dev(tx), to_dev(z), snr[s:s + 1], prec=prec, llr=True)
+        ml1, Lm1 = ctx.sweep_maxlog(c, tx_dev(tx), to_dev(z), snr[s:s + 1], prec=prec, llr=True)
+        ctx.sync()
+        assert torch.equal(L[s], L1[0]) and torch.equal(Lm[s], Lm1[0])
+        # the sums over samples may be grouped otherwise
+        np.testing.assert_allclose(st[s].cpu().numpy(), st1[0].cpu().numpy(), rtol=1e-11, atol=1e-13)
+        np.testing.assert_allclose(ml[s].cpu().numpy(), ml1[0].cpu().numpy(), rtol=1e-11, atol=1e-13)
+    c.close()
