@@ -42,7 +42,7 @@ FEC_THRESHOLD = [3.8e-3, 2.0e-2]
 # unchanged.
 FIRST_TIER_SOURCES = ("device_common.h", "mfma_kernels.h", "mfma_wide.h", "mfma_inst_f16_0.hip",
                       "mfma_inst_bf16_0.hip", "vec_kernels.h", "vec_inst_f32_0.hip", "air_host.hip",
-                      "host_state.h", "tier2_list.h", "exact_rule.h")
+                      "host_state.h", "tier2_list.h", "tail.h", "exact_rule.h")
 
 
 def source_hash() -> str:

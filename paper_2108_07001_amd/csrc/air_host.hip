@@ -7,6 +7,7 @@
 #include "mfma_wide.h"
 #include "hd_kernels.h"
 #include "aux_kernels.h"
+#include "tail.h"
 
 #include <cmath>
 #include <cstring>
@@ -18,10 +19,9 @@ namespace air {
 
 // Vector-kernel launchers, one per (type, D), defined in vec_inst_*.hip
 // (arguments: launch, grid, where, max-log form, part: 0 the first tier, 1
-// the FP32 second tier; the next call's words where no reduction follows).
-using VecFn = hipError_t (*)(const DemapArgs&, int, const Launch&, bool, int, CallWords*);
-#define AIR_DECL(tag, D) \
-  hipError_t launch_vec_##tag##_d##D(const DemapArgs&, int, const Launch&, bool, int, CallWords*);
+// the FP32 second tier).
+using VecFn = hipError_t (*)(const DemapArgs&, int, const Launch&, bool, int);
+#define AIR_DECL(tag, D) hipError_t launch_vec_##tag##_d##D(const DemapArgs&, int, const Launch&, bool, int);
 #define AIR_DECL_ALL(tag)                                                                        \
   AIR_DECL(tag, 1) AIR_DECL(tag, 2) AIR_DECL(tag, 3) AIR_DECL(tag, 4) AIR_DECL(tag, 5)          \
   AIR_DECL(tag, 6) AIR_DECL(tag, 7) AIR_DECL(tag, 8) AIR_DECL(tag, 9) AIR_DECL(tag, 10)         \
@@ -93,6 +93,12 @@ static const MfmaFn kMfmaBF16[kMaxD + 1] = {
     AIR_FN(bf16, 16)};
 #undef AIR_FN
 
+// Per-block sums that the last block of a short launch reduces itself; every
+// block takes a ticket for it, ~10 ns each in turn, so that with a few hundred
+// blocks the reduction kernel is faster (4-D/16 at one SNR point: 40 + 40 blocks
+// 27.5 -> 23.0 us, 391 + 391 blocks 27.2 -> 31.6 us).
+constexpr int64_t kTailSums = 160;
+
 // Grid of a matrix-core launch: 4 waves per block, one pair of 32-sample
 // tiles (64 samples) per wave and round.
 static int mfma_grid(int64_t N) {
@@ -113,63 +119,34 @@ static int vec_grid(int64_t N, int M = 0, bool llr_only = false) {
 }
 
 // Fixed-order reduction of the per-block partials of one launch: block s
-// reduces SNR point s; wave q of it sums quantity q over the demapping blocks
-// (lane l takes blocks l, l + 64, ...; then a fixed butterfly), so the result
-// does not depend on timing. stats[4 s + q] = MI, GMI, SE_MI, SE_GMI; NaN if
-// a tx index was invalid. Block 0 folds this call's error into the sticky word
-// and zeroes the next call's words.
+// reduces SNR point s (finish_point). Block 0 folds this call's error into the
+// sticky word and zeroes the next call's words.
 __global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ partials,
                                                      const double* __restrict__ t2_partials,
-                                                     int nblocks, int nblocks2, int64_t N, int M, int m,
-                                                     double* stats, const CallWords* call,
-                                                     CallWords* next, int* sticky, int no_mi) {
-  __shared__ double sums[4];
-  const int s = blockIdx.x;
-  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double t = 0.0;
-  // each lane's blocks (at most kMaxGrid / 64 = 24 per list) loaded at once,
-  // then added in block order
-  constexpr int kPer = kMaxGrid / 64;
-  const double* p = partials + ((int64_t)s * 4 + q) * nblocks;
-  double v[kPer], v2[kPer];
-  const double* p2 = t2_partials ? t2_partials + ((int64_t)s * 4 + q) * nblocks2 : nullptr;
+                                                     int nblocks, int64_t N, int M, int m, FinishArgs f) {
+  const int bad = f.call->err;
+  finish_point(blockIdx.x, N, M, m, bad != 0, f.no_mi, f.stats, [&](int s, int q, int lane) {
+    // each lane's blocks (at most kMaxGrid / 64 = 24 per list) loaded at once,
+    // then added in block order
+    constexpr int kPer = kMaxGrid / 64;
+    const double* p = partials + ((int64_t)s * 4 + q) * nblocks;
+    const double* p2 = t2_partials + ((int64_t)s * 4 + q) * f.blocks2;
+    double v[kPer], v2[kPer];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    v[i] = lane + 64 * i < nblocks ? p[lane + 64 * i] : 0.0;
-    v2[i] = p2 && lane + 64 * i < nblocks2 ? p2[lane + 64 * i] : 0.0;
-  }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) t += v[i];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) t += v2[i];
-  t = wave_sum(t);
-  if (lane == 0) sums[q] = t;
-  __syncthreads();
-  const int bad = call->err;
-  if (threadIdx.x == 0) {
-    if (stats) {
-      const double n = (double)N;
-      const double su = sums[0], sv = sums[1], suu = sums[2], svv = sums[3];
-      double mi = log2((double)M) - su / n;
-      double gmi = (double)m - sv / n;
-      double se_mi = __builtin_nan(""), se_gmi = __builtin_nan("");
-      if (N > 1) {
-        const double vu = (suu - su * su / n) / (n - 1.0);
-        const double vv = (svv - sv * sv / n) / (n - 1.0);
-        se_mi = sqrt((vu > 0.0 ? vu : 0.0) / n);
-        se_gmi = sqrt((vv > 0.0 ? vv : 0.0) / n);
-      }
-      if (no_mi) mi = se_mi = __builtin_nan("");       // max-log: no symbol-wise MI
-      if (bad) mi = gmi = se_mi = se_gmi = __builtin_nan("");
-      stats[4 * s + 0] = mi;
-      stats[4 * s + 1] = gmi;
-      stats[4 * s + 2] = se_mi;
-      stats[4 * s + 3] = se_gmi;
+    for (int i = 0; i < kPer; ++i) {
+      v[i] = lane + 64 * i < nblocks ? p[lane + 64 * i] : 0.0;
+      v2[i] = lane + 64 * i < f.blocks2 ? p2[lane + 64 * i] : 0.0;
     }
-    if (s == 0) {
-      if (bad) atomicOr(sticky, bad);
-      clear_call_words(next);
-    }
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) t += v[i];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) t += v2[i];
+    return t;
+  });
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    if (bad) atomicOr(f.sticky, bad);
+    clear_call_words(f.next);
   }
 }
 
@@ -458,15 +435,26 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   a.err = &ctx->call->err;
   a.recomputed = &ctx->call->recomputed;
   a.exact = &ctx->call->exact;
-  // an LLR-only call of the small sets ends with its one kernel (no error to
-  // fold, no sums to reduce)
-  const bool one_kernel = small && !tx;
+  const bool tier2 = (mfma && !maxlog) || vec_t2;
+  const int grid2 = tier2 ? t2_grid(grid, c->M) : 0;
+  a.blocks1 = grid;
+  a.fin.call = ctx->call;
+  a.fin.next = next;
+  a.fin.sticky = ctx->sticky;
+  a.fin.ticket = ctx->ticket;
+  a.fin.blocks2 = grid2;
+  a.fin.no_mi = maxlog ? 1 : 0;
   for (int s0 = 0; s0 < S; s0 += snr_per_launch) {
     const int ns = (S - s0 < snr_per_launch) ? S - s0 : snr_per_launch;
     a.S = ns;
     a.s_per = (ns + snr_slices(grid, ns) - 1) / snr_slices(grid, ns);
     fill_snr(a.snr, c, snr_db + s0, ns, aux);
     a.llr = llr ? (void*)((char*)llr + (size_t)s0 * N * c->m * tsz) : nullptr;
+    a.fin.stats = stats ? stats + 4 * s0 : nullptr;
+    // the ends of short launches (tail.h)
+    const bool tail = (small && tx) || tier2;
+    a.fin.in_last_block = tail && ns * (int64_t)(grid + grid2) <= kTailSums;
+    a.fin.short_lists = tier2 && ns == 1 && grid * 4 <= kShortWaves;
     // timed: the demapping kernel's dispatch itself sets the two events; they
     // serve timing only, so they skip the system-scope fence (a cache
     // write-back that idles the stream around the kernel: 5.8 -> 2.3 us per
@@ -485,18 +473,18 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
       lt.stop = ctx->ev[ctx->ev_used + 1];
       ctx->ev_used += 2;
     }
-    e = mfma ? mfn(a, rec, grid, lt, maxlog ? 2 : 0) : vfn(a, grid, lt, maxlog, 0, one_kernel ? next : nullptr);
+    e = mfma ? mfn(a, rec, grid, lt, maxlog ? 2 : 0) : vfn(a, grid, lt, maxlog, 0);
     if (e != hipSuccess) return hip_fail(ctx, e, "demapping kernel launch");
-    if (one_kernel) continue;
-    const bool tier2 = (mfma && !maxlog) || vec_t2;
     if (tier2) {
       const Launch l2{ctx->stream, nullptr, nullptr};
-      e = mfma ? mfn(a, rec, grid, l2, 1) : vfn(a, grid, l2, false, 1, nullptr);
+      e = mfma ? mfn(a, rec, grid, l2, 1) : vfn(a, grid, l2, false, 1);
       if (e != hipSuccess) return hip_fail(ctx, e, "second-tier launch");
     }
-    hipLaunchKernelGGL(finish_kernel, dim3(ns), dim3(256), 0, ctx->stream, ctx->partials,
-                       tier2 ? ctx->t2_partials : nullptr, grid, t2_grid(grid, c->M), N, c->M, c->m,
-                       stats ? stats + 4 * s0 : nullptr, ctx->call, next, ctx->sticky, maxlog ? 1 : 0);
+    // done already: by the last demapping kernel's last block, or nothing to do
+    // after the one kernel of an LLR-only call of the small sets
+    if (a.fin.in_last_block || (small && !tx)) continue;
+    hipLaunchKernelGGL(finish_kernel, dim3(ns), dim3(256), 0, ctx->stream, ctx->partials, ctx->t2_partials, grid, N,
+                       c->M, c->m, a.fin);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "reduction kernel launch");
   }
@@ -640,6 +628,8 @@ air_status air_create(air_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipMalloc(&ctx->t2_tot, sizeof(unsigned int) * kMaxSnrPerLaunch);
     if (e == hipSuccess) e = hipMalloc(&ctx->calls, 2 * sizeof(CallWords));
     if (e == hipSuccess) e = hipMalloc(&ctx->sticky, sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&ctx->ticket, sizeof(unsigned int));
+    if (e == hipSuccess) e = hipMemset(ctx->ticket, 0, sizeof(unsigned int));
     if (e == hipSuccess) e = hipMalloc(&ctx->small, sizeof(double) * kSmallDoubles);
     if (e == hipSuccess) e = hipMemset(ctx->calls, 0, 2 * sizeof(CallWords));
     ctx->call = ctx->calls;
@@ -666,6 +656,7 @@ void air_destroy(air_ctx* ctx) {
   (void)hipFree(ctx->partials);
   (void)hipFree(ctx->calls);
   (void)hipFree(ctx->sticky);
+  (void)hipFree(ctx->ticket);
   free_t2(ctx);
   (void)hipFree(ctx->t2_partials);
   (void)hipFree(ctx->t2_tot);

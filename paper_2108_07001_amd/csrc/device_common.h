@@ -64,6 +64,16 @@ inline int snr_slices(int gx, int S) {
   return n < 1 ? 1 : (n < S ? n : S);
 }
 
+// A value for, and from, another block of the same launch.
+template <typename T>
+__device__ __forceinline__ void to_other_block(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T from_other_block(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Zeroes the words of the next call (one thread).
 __device__ inline void clear_call_words(CallWords* next) {
   if (next) {
@@ -80,6 +90,21 @@ struct SnrTable {
   double c[kMaxSnrPerLaunch];       // 1 / (2 sigma^2 ln 2)
   float sigmaf[kMaxSnrPerLaunch];
   float cf[kMaxSnrPerLaunch];
+};
+
+// What ends a call: the reduction of the per-block sums into statistics and the
+// hand-over of the call words, by finish_kernel or, for short launches, by the
+// last block of the call's last demapping kernel (tail.h).
+struct FinishArgs {
+  double* stats;                    // [S][4] of the launch, or nullptr
+  const CallWords* call;
+  CallWords* next;                  // zeroed for the next call
+  int* sticky;
+  unsigned int* ticket;             // blocks done; zero between launches
+  int blocks2;                      // blocks of the second tier's partials, 0 for none
+  int no_mi;                        // max-log: no symbol-wise MI
+  int in_last_block;                // 1: the last kernel's last block finishes the call
+  int short_lists;                  // 1: the second tier reads the first one's lists itself
 };
 
 // Arguments of every demapping kernel.
@@ -101,6 +126,7 @@ struct DemapArgs {
   // second tier (matrix-core forms and the FP32 vector kernel)
   unsigned long long* t2_list;      // [S][waves][tpw]: sample tile (32 bits) | lane mask (32)
   double* t2_partials;              // [S][4][gridDim.x], as partials, from the second tier
+  int blocks1;                      // gridDim.x of the first tier
   int t2_tpw;                       // list slots per (SNR point, wave)
   unsigned int* t2_nitem;           // [S][waves]: samples flagged in each wave's list
   // the flagged samples gathered per SNR point: point s's samples, in (wave,
@@ -108,6 +134,7 @@ struct DemapArgs {
   uint32_t* t2_items;               // sample indices
   int64_t t2_cap;                   // entries of t2_items per SNR point (waves x tpw x 32)
   unsigned int* t2_tot;             // [S]: samples flagged at each SNR point
+  FinishArgs fin;
   SnrTable snr;
 };
 

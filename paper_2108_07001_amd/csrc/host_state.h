@@ -29,6 +29,7 @@ struct air_ctx {
   air::CallWords* call = nullptr;  // the slot of the current (or last) call
   bool next_zeroed = true;         // the other slot is known to hold zeros
   int* sticky = nullptr;         // tx-range error seen since the last air_sync
+  unsigned int* ticket = nullptr;  // blocks done of the launch in flight (tail.h)
   // second tier of the matrix-core path: per-wave tile lists and their counts
   unsigned long long* t2_list = nullptr;
   double* t2_partials = nullptr; // kMaxSnrPerLaunch x 4 x kMaxGrid

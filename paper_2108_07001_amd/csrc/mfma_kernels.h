@@ -53,7 +53,7 @@
 // result is independent of timing.
 #pragma once
 #include "device_common.h"
-#include "tier2_list.h"
+#include "tail.h"
 
 namespace air {
 
@@ -869,7 +869,15 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
   const int S = a.S;
   // the SNR runs in the tile sequence: lane s holds run s's padded start and its
   // sample count; T tiles in all
-  const unsigned int tot_l = lane < S ? a.t2_tot[lane] : 0u;
+  __shared__ unsigned int pre[kShortWaves];
+  const bool short_lists = a.fin.short_lists != 0;
+  unsigned int tot_l;
+  if (short_lists) {
+    const unsigned int tot = short_scan(a, pre);
+    tot_l = lane == 0 ? tot : 0u;
+  } else {
+    tot_l = lane < S ? a.t2_tot[lane] : 0u;
+  }
   uint64_t pstart_l = 0, run = 0;
   for (int s = 0; s < S; ++s) {
     if (lane == s) pstart_l = run;
@@ -878,7 +886,8 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
   const int64_t T = (int64_t)(run >> 5);
   if ((int64_t)blockIdx.x * waves >= T) {
     // no tile reaches this block: zero partials, and no tables to stage
-    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) a.t2_partials[(int64_t)i * gridDim.x + blockIdx.x] = 0.0;
+    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), 0.0);
+    finish_in_last_block(a, a.blocks1);
     return;
   }
   Tables<BF> tb{a.lab, xl, rec};
@@ -943,7 +952,10 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
     const unsigned int cnt = __builtin_amdgcn_readlane(tot_l, s);
     const uint64_t pos = p0 + (uint64_t)j;
     const bool has = pos - start < (uint64_t)cnt;
-    const int64_t sn = has ? (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)] : -1;
+    int64_t sn = -1;
+    if (has)
+      sn = short_lists ? (int64_t)short_item(a, pre, (unsigned int)pos)
+                       : (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)];
     items += (unsigned long long)__builtin_popcountll(__ballot(has && h == 0));
     const SampleParams sp = sample_params(a, s);
     TileInput<D> ti;
@@ -976,8 +988,9 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
   for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    a.t2_partials[(int64_t)i * gridDim.x + blockIdx.x] = t;
+    to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), t);
   }
+  finish_in_last_block(a, a.blocks1);
 }
 
 }  // namespace air

@@ -90,6 +90,7 @@ __host__ __device__ inline int t2_grid(int grid, int M) { return M >= 512 || gri
 
 // The first tier's flagged samples gathered per SNR point, with their counts.
 inline void launch_t2_collect(const DemapArgs& a, int grid, hipStream_t st) {
+  if (a.fin.short_lists) return;       // read by the second tier as they are
   const int W = grid * 4;
   hipLaunchKernelGGL(t2_collect, dim3((unsigned)((W + 255) / 256), (unsigned)a.S), dim3(256), 0, st, a.t2_nitem,
                      a.t2_list, W, a.t2_tpw, a.t2_cap, a.t2_tot, a.t2_items);

@@ -4,9 +4,8 @@
 
 namespace air {
 #define AIR_VEC_INST(D) \
-  hipError_t launch_vec_f32_d##D(const DemapArgs& a, int g, const Launch& l, bool ml, int part, \
-                                  CallWords* next) { \
-    return launch_vec_td<float, D>(a, g, l, ml, part, next); \
+  hipError_t launch_vec_f32_d##D(const DemapArgs& a, int g, const Launch& l, bool ml, int part) { \
+    return launch_vec_td<float, D>(a, g, l, ml, part); \
   }
 AIR_VEC_INST(13)
 AIR_VEC_INST(14)

@@ -28,7 +28,7 @@
 // spans ~1000 log2 units) and finishes starved items on the exact path.
 #pragma once
 #include "device_common.h"
-#include "tier2_list.h"
+#include "tail.h"
 
 namespace air {
 
@@ -303,8 +303,7 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
 // logarithms of ~30 instructions each are most of it). Terms, sums and outputs
 // per item are those of demap_vec and demap_vec_t2.
 template <typename T, int D, int G>
-__global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, const T* __restrict__ xl,
-                                                          CallWords* next) {
+__global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, const T* __restrict__ xl) {
   constexpr int m = Log2G<G>::v;
   constexpr bool F32 = sizeof(T) == 4;
   extern __shared__ double acc_lds[];            // [waves][s_per][4]
@@ -530,13 +529,14 @@ __global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, con
     for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
       double t = 0.0;
       for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
-      a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
+      to_other_block(a.partials + ((int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x), t);
     }
   if (threadIdx.x == 0) {
     if (counts[0]) atomicAdd(a.recomputed, (unsigned long long)counts[0]);
     if (counts[1]) atomicAdd(a.exact, (unsigned long long)counts[1]);
-    if (next && blockIdx.x == 0 && blockIdx.y == 0) clear_call_words(next);
+    if (!a.tx && blockIdx.x == 0 && blockIdx.y == 0) clear_call_words(a.fin.next);
   }
+  finish_in_last_block(a, gridDim.x);
 }
 
 // Second tier of the FP32 vector kernel. The first tier's flagged samples,
@@ -562,7 +562,15 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
   const int S = a.S;
   // the SNR runs in the tile sequence: lane s holds run s's padded start and
   // its sample count
-  const unsigned int tot_l = lane < S ? a.t2_tot[lane] : 0u;
+  __shared__ unsigned int pre[kShortWaves];
+  const bool short_lists = a.fin.short_lists != 0;
+  unsigned int tot_l;
+  if (short_lists) {
+    const unsigned int tot = short_scan(a, pre);
+    tot_l = lane == 0 ? tot : 0u;
+  } else {
+    tot_l = lane < S ? a.t2_tot[lane] : 0u;
+  }
   uint64_t pstart_l = 0, run = 0;
   for (int s = 0; s < S; ++s) {
     if (lane == s) pstart_l = run;
@@ -571,7 +579,8 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
   const int64_t T = (int64_t)(run >> 6);
   if ((int64_t)blockIdx.x * waves >= T) {
     // no tile reaches this block
-    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) a.t2_partials[(int64_t)i * gridDim.x + blockIdx.x] = 0.0;
+    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), 0.0);
+    finish_in_last_block(a, a.blocks1);
     return;
   }
   const int M = a.M, m = a.m;
@@ -636,7 +645,8 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
     float* lout = nullptr;
     float u = 0.f, v = 0.f;
     if (has) {
-      n = (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)];
+      n = short_lists ? (int64_t)short_item(a, pre, (unsigned int)pos)
+                      : (int64_t)a.t2_items[(int64_t)s * a.t2_cap + (int64_t)(pos - start)];
       // flagged samples are live: a transmitted index, if any, is in range
       tl = a.tx ? (int)a.lab[a.tx[n]] : -1;
       const float c = a.snr.cf[s];
@@ -737,16 +747,16 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
   for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    a.t2_partials[(int64_t)i * gridDim.x + blockIdx.x] = t;
+    to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), t);
   }
+  finish_in_last_block(a, a.blocks1);
 }
 
 // part 0: the first tier (exact or, with ml, max-log); part 1 (FP32 exact form
 // of more than 16 points only): the gather of the first tier's lists and the
-// second tier. `next`: the next call's words for a launch that no reduction
-// follows, else null. The events of `l` time part 0's kernel only.
+// second tier. The events of `l` time part 0's kernel only.
 template <typename T, int D, int G>
-hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml, int part, CallWords* next) {
+hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml, int part) {
   const uint32_t acc = (uint32_t)(sizeof(double) * (kBlock / 64) * a.s_per * 4);
   const dim3 g(grid, (a.S + a.s_per - 1) / a.s_per);
   if (ml) {
@@ -755,7 +765,7 @@ hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml
   }
   if (a.M <= 16) {
     if (a.M != G || part != 0) return hipErrorInvalidValue;
-    launch_kernel(l, demap_vec_small<T, D, G>, g, dim3(kBlock), acc, a, static_cast<const T*>(a.xl), next);
+    launch_kernel(l, demap_vec_small<T, D, G>, g, dim3(kBlock), acc, a, static_cast<const T*>(a.xl));
     return hipGetLastError();
   }
   if constexpr (G == 16) {
@@ -780,12 +790,12 @@ hipError_t launch_vec_one(const DemapArgs& a, int grid, const Launch& l, bool ml
 
 // ml: the max-log form.
 template <typename T, int D>
-hipError_t launch_vec_td(const DemapArgs& a, int grid, const Launch& l, bool ml, int part, CallWords* next) {
+hipError_t launch_vec_td(const DemapArgs& a, int grid, const Launch& l, bool ml, int part) {
   switch (a.M >= 16 ? 16 : a.M) {
-    case 2: return launch_vec_one<T, D, 2>(a, grid, l, ml, part, next);
-    case 4: return launch_vec_one<T, D, 4>(a, grid, l, ml, part, next);
-    case 8: return launch_vec_one<T, D, 8>(a, grid, l, ml, part, next);
-    default: return launch_vec_one<T, D, 16>(a, grid, l, ml, part, next);
+    case 2: return launch_vec_one<T, D, 2>(a, grid, l, ml, part);
+    case 4: return launch_vec_one<T, D, 4>(a, grid, l, ml, part);
+    case 8: return launch_vec_one<T, D, 8>(a, grid, l, ml, part);
+    default: return launch_vec_one<T, D, 16>(a, grid, l, ml, part);
   }
 }
 

@@ -305,3 +305,40 @@ def test_point_loops_of_four_tiles(ctx, M, D, N, prec):
     _report(f"M{M} D{D} N{N} {prec}", st, L, ref)
     assert_stats(st, ref["stats"], se_rel=2e-2)
     assert_llr(L, ref["llr"], LLR_BAR[prec])
+
+
+@pytest.mark.parametrize("M,D", [(16, 4), (64, 4), (256, 3), (2048, 8)])
+@pytest.mark.parametrize("N", [1, 64, 65, 5000, 16384, 16385, 70000])
+@pytest.mark.parametrize("prec", ["fp16x3", "fp32"])
+def test_short_calls_end_in_the_last_block(ctx, M, D, N, prec):
+    # one SNR point and at most 256 waves: the second tier reads the lists
+    # itself and its last block reduces the sums; the two sides of those limits,
+    # with no, some and all items listed, against the same points in one sweep
+    # (gathered lists, reduction kernel), several calls in turn
+    X, lab = inputs.random_constellation(M + 5 * D, M, D)
+    tx, z = inputs.random_block(N + M, M, N, D)
+    c = ctx.const(X, lab)
+    t, zd = tx_dev(tx), to_dev(z)
+    snr = np.array([2.0, 17.0, 21.0, 28.0])
+    st, L = ctx.sweep(c, t, zd, snr, prec=prec, llr=True)
+    ctx.sync()
+    rec = ctx.last_recomputed()
+    for k in (0, 1, 2, 3, 1):
+        s1, L1 = ctx.sweep(c, t, zd, snr[k:k + 1], prec=prec, llr=True)
+        ctx.sync()
+        # (from 128 points on, the rounds a wave lists without forming them may differ)
+        if M < 128:
+            assert torch.equal(L1[0], L[k])
+        np.testing.assert_allclose(L1[0].cpu().numpy(), L[k].cpu().numpy(), rtol=2e-4, atol=2e-4)
+        np.testing.assert_allclose(s1[0].cpu().numpy(), st[k].cpu().numpy(), rtol=1e-5, atol=1e-5, equal_nan=True)
+    bad = tx.astype(np.int64).copy()
+    bad[N // 2] = M
+    sb, _ = ctx.sweep(c, tx_dev(bad), zd, snr[:1], prec=prec, llr=True)
+    with pytest.raises(air.AirError):
+        ctx.sync()
+    assert torch.isnan(sb).all()
+    s2, _ = ctx.sweep(c, t, zd, snr[:1], prec=prec, llr=True)
+    ctx.sync()
+    assert torch.equal(torch.nan_to_num(s2), torch.nan_to_num(ctx.sweep(c, t, zd, snr[:1], prec=prec, llr=True)[0]))
+    assert N == 1 or rec > 0
+    c.close()
