@@ -107,13 +107,15 @@ static int mfma_grid(int64_t N) {
   return (int)(g < kMaxGrid ? g : kMaxGrid);
 }
 
-// Grid of a vector-kernel launch: one sample per thread and round. Sets of
-// M >= 32 points take up to kMaxGrid blocks; for the small sets, whose
-// samples are cheap, the per-block reductions weigh more and 1024 blocks
-// measured faster (2-D QAM-4 buffers of 2^20 symbols: 1536 blocks, 25 %
-// slower). Their LLR-only calls write no partial sums.
-static int vec_grid(int64_t N, int M = 0, bool llr_only = false) {
-  const int64_t cap = M >= 32 ? kMaxGrid : (llr_only ? 2048 : 1024);
+// Grid of a vector-kernel launch: one sample per thread and round. For the sets
+// of at most 16 points, whose samples are cheap, the per-block reductions weigh
+// more, and 1024 blocks measured faster than 1536 (2-D QAM-4 buffers of 2^20
+// symbols: 25 %); their LLR-only calls write no partial sums. Larger sets take up
+// to kMaxGrid blocks at one SNR point, and at several 1024 that the points are
+// dealt out to (8-D/2048, 1e6 samples: 5 points 4.78 -> 4.48 ms with 2 x 1024, one
+// point 0.96 -> 1.09 ms with 1024).
+static int vec_grid(int64_t N, int M = 0, bool llr_only = false, int S = 1) {
+  const int64_t cap = M > 16 ? (S > 1 ? 1024 : kMaxGrid) : (llr_only ? 2048 : 1024);
   const int64_t g = (N + kBlock - 1) / kBlock;
   return (int)(g < cap ? g : cap);
 }
@@ -362,7 +364,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   const size_t tsz = fp64 ? sizeof(double) : sizeof(float);
   // matrix-core tiles hold 16 or 32 points; smaller sets run the FP32 vector kernel
   const bool mfma = (prec == AIR_FP16X3 || prec == AIR_BF16X3) && c->M >= 16;
-  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M, !tx);
+  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M, !tx, S);
   const VecFn vfn = fp64 ? kVecF64[c->D] : kVecF32[c->D];
   const MfmaFn mfn = prec == AIR_BF16X3 ? kMfmaBF16[c->D] : kMfmaF16[c->D];
   const void* rec = prec == AIR_BF16X3 ? (const void*)c->rec_bf16 : (const void*)c->rec_f16;
@@ -552,6 +554,7 @@ air_status run_hd(air_ctx* ctx, const air_const* c, const float* in, const uint3
   for (int s0 = 0; s0 < S; s0 += kMaxSnrPerLaunch) {
     const int ns = (S - s0 < kMaxSnrPerLaunch) ? S - s0 : kMaxSnrPerLaunch;
     a.S = ns;
+    a.s_per = (ns + snr_slices(grid, ns) - 1) / snr_slices(grid, ns);
     for (int s = 0; s < ns; ++s) {
       double sigma = 0.0, cc = 0.0;
       if (sweep) snr_scalars(c, snr_db[s0 + s], sigma, cc);
@@ -599,7 +602,7 @@ air_status run_noise_var(air_ctx* ctx, const air_const* c, const void* Y, const 
                        &ctx->call->err);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e, "noise estimate launch");
-  hipLaunchKernelGGL(noise_var_finish, dim3(1), dim3(64), 0, ctx->stream, ctx->partials, grid, c->D, N,
+  hipLaunchKernelGGL(noise_var_finish, dim3(1), dim3(64 * c->D), 0, ctx->stream, ctx->partials, grid, c->D, N,
                      var, &ctx->call->err, next, ctx->sticky);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e, "noise estimate reduction launch");

@@ -27,6 +27,7 @@ struct HdArgs {
   int* err;                   // set when a transmitted index >= M is seen
   int64_t N;
   int M, S, sweep;
+  int s_per;                  // SNR points per block (blockIdx.y: a run of them)
   float sigma[kMaxSnrPerLaunch];
 };
 
@@ -39,7 +40,9 @@ __global__ __launch_bounds__(kBlock) void hd_kernel(const HdArgs a) {
   const int NG = M / G;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const float* __restrict__ xl = a.xl;
-  for (int s = 0; s < a.S; ++s) {
+  const int s0 = blockIdx.y * a.s_per;
+  const int s1 = s0 + a.s_per < a.S ? s0 + a.s_per : a.S;
+  for (int s = s0; s < s1; ++s) {
     unsigned int se = 0, be = 0;
     for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n < a.N; n += stride) {
       int tl = -1;
@@ -102,11 +105,12 @@ __global__ __launch_bounds__(kBlock) void hd_kernel(const HdArgs a) {
 
 template <int D>
 hipError_t launch_hd_d(const HdArgs& a, int grid, hipStream_t st) {
+  const dim3 g(grid, (a.S + a.s_per - 1) / a.s_per);
   switch (a.M >= 16 ? 16 : a.M) {
-    case 2: hipLaunchKernelGGL((hd_kernel<D, 2>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((hd_kernel<D, 4>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((hd_kernel<D, 8>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    default: hipLaunchKernelGGL((hd_kernel<D, 16>), dim3(grid), dim3(kBlock), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((hd_kernel<D, 2>), g, dim3(kBlock), 0, st, a); break;
+    case 4: hipLaunchKernelGGL((hd_kernel<D, 4>), g, dim3(kBlock), 0, st, a); break;
+    case 8: hipLaunchKernelGGL((hd_kernel<D, 8>), g, dim3(kBlock), 0, st, a); break;
+    default: hipLaunchKernelGGL((hd_kernel<D, 16>), g, dim3(kBlock), 0, st, a); break;
   }
   return hipGetLastError();
 }

@@ -151,7 +151,9 @@ __global__ __launch_bounds__(256, D <= 8 ? 3 : 2) void hd_mfma(const HdArgs a, c
   const int64_t npairs = (ntiles + 1) >> 1;
   const int64_t wstride = (int64_t)gridDim.x * waves;
   const int64_t wgid = (int64_t)blockIdx.x * waves + wave;
-  for (int s = 0; s < a.S; ++s) {
+  const int s0 = blockIdx.y * a.s_per;
+  const int s1 = s0 + a.s_per < a.S ? s0 + a.s_per : a.S;
+  for (int s = s0; s < s1; ++s) {
     unsigned int se = 0, be = 0;
     for (int64_t q = wgid; q < npairs; q += wstride) {
       // the lane's own sample, formed as hd_kernel forms it
@@ -283,11 +285,12 @@ template <int D>
 hipError_t launch_hd_mfma_d(const HdArgs& a, const void* rec, float R2, int grid, hipStream_t st) {
   typedef MfmaOp<false>::vec V;
   const V* r = static_cast<const V*>(rec);
+  const dim3 g(grid, (a.S + a.s_per - 1) / a.s_per);
   const int64_t tb = hd_table_bytes(a.M, D);
   if (tb <= 40 * 1024)
-    hipLaunchKernelGGL((hd_mfma<D, true>), dim3(grid), dim3(256), (size_t)tb, st, a, r, R2);
+    hipLaunchKernelGGL((hd_mfma<D, true>), g, dim3(256), (size_t)tb, st, a, r, R2);
   else
-    hipLaunchKernelGGL((hd_mfma<D, false>), dim3(grid), dim3(256), 0, st, a, r, R2);
+    hipLaunchKernelGGL((hd_mfma<D, false>), g, dim3(256), 0, st, a, r, R2);
   return hipGetLastError();
 }
 
