@@ -667,7 +667,41 @@ __device__ __forceinline__ void tier1_tile(const SampleTile<D, BF>& smp, const T
   // run (other waves on the SIMD cover the product latency)
   TileSums<float, NE> ts;
   ts.init();
-  {
+  if (!HALF && NT >= 4) {
+    // four tiles per step, the products a tile ahead (as tier2_tile's QUAD form)
+    if constexpr (!HALF) {
+      constexpr int NSET = NK <= 2 ? 2 : 1;
+      ts.zero();
+      V rs[NSET][NK];
+      auto load = [&](V (&A)[NK], int t) {
+        const V* rp = rec_row<BF, HALF, NK>(tb.rec, t, j, h);
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
+      };
+      load(rs[0], 0);
+      if (NSET == 2) load(rs[NSET - 1], 1);
+      float16_t acc = smp.product(rs[0]);
+      load(rs[0], NSET);
+      for (int t = 0; t < NT; t += 4) {
+        float ct[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
+          float ev[NE];
+#pragma unroll
+          for (int e = 0; e < NE; ++e) ev[e] = Real<float>::exp2(acc[e]);
+          __builtin_amdgcn_sched_barrier(0);
+          acc = smp.product(A);
+          load(A, (t + u + 1 + NSET) & (NT - 1));
+          // keeps the loads here (else merged into loads before their use)
+          asm volatile("" ::: "memory");
+          ct[u] = ts.tile(ev);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        ts.quad(ct, t >> 2, ntb);
+      }
+    }
+  } else {
     V A[NK];
     const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
 #pragma unroll
@@ -733,7 +767,7 @@ __device__ __forceinline__ void tier1_tile(const SampleTile<D, BF>& smp, const T
 // flagged finish it here, or on the exact path when even this frame starves
 // (or the sample side left the f16 range). Returns whether this lane took the
 // exact path.
-template <int D, bool BF, bool HALF, bool QUAD = false>
+template <int D, bool BF, bool HALF, int QUAD = 0>
 __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const Tables<BF>& tb,
                                            const ExactArgs<float>& ex, bool has_tx, bool flagged,
                                            int j, int h, int m, int NT, int ntb, float* lout,
@@ -753,59 +787,65 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
   };
   TileSums<double, NE> ts;
   ts.init();
-  if constexpr (!QUAD) {
-    V A[NK];
-    const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
-    for (int t = 0; t < NT; ++t) {
-      const float16_t acc = smp.product(A);
-      if (t + 1 < NT) {
-        const V* rq = rec_row<BF, HALF, NK>(tb.rec, t + 1, j, h);
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) A[kk] = rq[2 * kk];
-      }
-      double ev[NE];
-#pragma unroll
-      for (int e = 0; e < NE; ++e) ev[e] = val64(acc[e]);
-      ts.add(ev, t, ntb);
-    }
-  } else {
-    // QUAD (M >= 128): four tiles per step, the products a tile ahead and the
-    // point records NSET tiles ahead (one tile's work does not cover an L2 read;
-    // past the end the tiles wrap, and those products are not used). Bound by
-    // VALU issue: 16 terms take 131 instructions (148 with a tile at a time,
-    // whose counter branches and waits for the products left the VALU idle
-    // 23 % of the time; now 13 %). 8-D/2048, 9.7e6 items: 6.95 -> 6.4 ms.
-    constexpr int NSET = NK <= 2 ? 2 : 1;
-    ts.zero();
-    V rs[NSET][NK];
-    auto load = [&](V (&A)[NK], int t) {
-      const V* rp = rec_row<BF, HALF, NK>(tb.rec, t, j, h);
+  // QUAD: 0 one tile at a time, 1 four (sets of 128 points and more), 2 by NT
+  const bool quads = !HALF && (QUAD == 1 || (QUAD == 2 && NT >= 4));
+  if (!quads) {
+    if constexpr (QUAD != 1) {
+      V A[NK];
+      const V* rp = rec_row<BF, HALF, NK>(tb.rec, 0, j, h);
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
-    };
-    load(rs[0], 0);
-    if (NSET == 2) load(rs[NSET - 1], 1);
-    float16_t acc = smp.product(rs[0]);
-    load(rs[0], NSET);
-    for (int t = 0; t < NT; t += 4) {
-      double ct[4];
+      for (int t = 0; t < NT; ++t) {
+        const float16_t acc = smp.product(A);
+        if (t + 1 < NT) {
+          const V* rq = rec_row<BF, HALF, NK>(tb.rec, t + 1, j, h);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
+          for (int kk = 0; kk < NK; ++kk) A[kk] = rq[2 * kk];
+        }
         double ev[NE];
 #pragma unroll
         for (int e = 0; e < NE; ++e) ev[e] = val64(acc[e]);
-        __builtin_amdgcn_sched_barrier(0);
-        acc = smp.product(A);
-        load(A, (t + u + 1 + NSET) & (NT - 1));
-        // keeps the loads here (else merged into loads before their use)
-        asm volatile("" ::: "memory");
-        ct[u] = ts.tile(ev);
-        __builtin_amdgcn_sched_barrier(0);
+        ts.add(ev, t, ntb);
       }
-      ts.quad(ct, t >> 2, ntb);
+    }
+  } else {
+    if constexpr (QUAD != 0 && !HALF) {
+      // four tiles per step, the products a tile ahead and the
+      // point records NSET tiles ahead (one tile's work does not cover an L2 read;
+      // past the end the tiles wrap, and those products are not used). Bound by
+      // VALU issue: 16 terms take 131 instructions (148 with a tile at a time,
+      // whose counter branches and waits for the products left the VALU idle
+      // 23 % of the time; now 13 %). 8-D/2048, 9.7e6 items: 6.95 -> 6.4 ms.
+      constexpr int NSET = NK <= 2 ? 2 : 1;
+      ts.zero();
+      V rs[NSET][NK];
+      auto load = [&](V (&A)[NK], int t) {
+        const V* rp = rec_row<BF, HALF, NK>(tb.rec, t, j, h);
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) A[kk] = rp[2 * kk];
+      };
+      load(rs[0], 0);
+      if (NSET == 2) load(rs[NSET - 1], 1);
+      float16_t acc = smp.product(rs[0]);
+      load(rs[0], NSET);
+      for (int t = 0; t < NT; t += 4) {
+        double ct[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
+          double ev[NE];
+#pragma unroll
+          for (int e = 0; e < NE; ++e) ev[e] = val64(acc[e]);
+          __builtin_amdgcn_sched_barrier(0);
+          acc = smp.product(A);
+          load(A, (t + u + 1 + NSET) & (NT - 1));
+          // keeps the loads here (else merged into loads before their use)
+          asm volatile("" ::: "memory");
+          ct[u] = ts.tile(ev);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        ts.quad(ct, t >> 2, ntb);
+      }
     }
   }
   const float arg_t = has_tx ? smp.transmitted_arg(tb.rec, j, h) : 0.f;
@@ -969,7 +1009,7 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
     float u, v;
     ExactArgs<float> ex = exact_args<float>(a, s);
     ex.xl = tb.xl;
-    const bool ex_lane = tier2_tile<D, BF, HALF, QUAD>(smp, tb, ex, a.tx != nullptr, flagged, j, h, m, NT, ntb,
+    const bool ex_lane = tier2_tile<D, BF, HALF, QUAD ? 1 : 0>(smp, tb, ex, a.tx != nullptr, flagged, j, h, m, NT, ntb,
                                                  lout, u, v);
     exact += (unsigned long long)__builtin_popcountll(__ballot(ex_lane));
     if (flagged && h == 0 && smp.tl >= 0) {

@@ -72,7 +72,7 @@ __device__ __forceinline__ SampleParams job_params(const JobDesc& jd) {
 constexpr int kDirectTile = 24;
 
 template <int D, bool BF, bool HALF>
-__global__ __launch_bounds__(256) void serve_tier1(const JobDesc* __restrict__ jobs, int njobs,
+__global__ __launch_bounds__(256, D <= 8 ? 3 : 2) void serve_tier1(const JobDesc* __restrict__ jobs, int njobs,
                                                    int64_t nitems) {
   typedef typename MfmaOp<BF>::vec V;
   typedef SampleTile<D, BF> ST;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void serve_tier1(const JobDesc* __restrict__ j
 }
 
 template <int D, bool BF, bool HALF>
-__global__ __launch_bounds__(256, D <= 12 ? 2 : 1) void serve_tier2(const JobDesc* __restrict__ jobs, int njobs,
+__global__ __launch_bounds__(256, 2) void serve_tier2(const JobDesc* __restrict__ jobs, int njobs,
                                                    int64_t nitems) {
   typedef typename MfmaOp<BF>::vec V;
   typedef SampleTile<D, BF> ST;
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256, D <= 12 ? 2 : 1) void serve_tier2(const JobDes
         const bool flagged = (mask >> j) & 1u;
         float* lout = (jd.llr && smp.valid) ? jd.llr + smp.n * m : nullptr;
         float u, v;
-        tier2_tile<D, BF, HALF>(smp, tb, ex, jd.tx != nullptr, flagged, j, h, m, NT, ntb, lout, u, v);
+        tier2_tile<D, BF, HALF, 2>(smp, tb, ex, jd.tx != nullptr, flagged, j, h, m, NT, ntb, lout, u, v);
         if (flagged && h == 0 && smp.tl >= 0) {
           const double du = (double)u, dv = (double)v;
           au += du;
