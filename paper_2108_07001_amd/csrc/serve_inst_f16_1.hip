@@ -4,9 +4,9 @@
 
 namespace air {
 #define AIR_SERVE_INST(D)                                                                       \
-  hipError_t launch_serve_f16_d##D(const JobDesc* j, int n, int64_t items, bool half, int g, \
+  hipError_t launch_serve_f16_d##D(const JobDesc* j, int n, int64_t items, int64_t units, bool half, int g, \
                                    hipStream_t s) {                                            \
-    return launch_serve_td<D, false>(j, n, items, half, g, s);                                  \
+    return launch_serve_td<D, false>(j, n, items, units, half, g, s);                                  \
   }
 AIR_SERVE_INST(5)
 AIR_SERVE_INST(6)

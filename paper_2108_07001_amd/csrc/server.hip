@@ -30,9 +30,9 @@
 namespace air {
 
 // Batched launchers, one per (operand type, D), defined in serve_inst_*.hip.
-using ServeFn = hipError_t (*)(const JobDesc*, int, int64_t, bool, int, hipStream_t);
+using ServeFn = hipError_t (*)(const JobDesc*, int, int64_t, int64_t, bool, int, hipStream_t);
 #define AIR_DECL(tag, D) \
-  hipError_t launch_serve_##tag##_d##D(const JobDesc*, int, int64_t, bool, int, hipStream_t);
+  hipError_t launch_serve_##tag##_d##D(const JobDesc*, int, int64_t, int64_t, bool, int, hipStream_t);
 #define AIR_DECL_ALL(tag)                                                                        \
   AIR_DECL(tag, 1) AIR_DECL(tag, 2) AIR_DECL(tag, 3) AIR_DECL(tag, 4) AIR_DECL(tag, 5)          \
   AIR_DECL(tag, 6) AIR_DECL(tag, 7) AIR_DECL(tag, 8) AIR_DECL(tag, 9) AIR_DECL(tag, 10)         \
@@ -176,7 +176,7 @@ struct Job {
   const air_const* c = nullptr;
   int cls = 0;                   // kernel class: D, operand type, 16-point form
   bool in_host = false, tx_host = false, llr_host = false;
-  int chunk = 1, nitems = 0;
+  int chunk = 1, nitems = 0, unit = 1, nunits = 0;
   size_t foot = 0, off = 0;      // arena block
   size_t o_in = 0, o_tx = 0, o_llr = 0, o_part = 0, o_list = 0, o_count = 0;
   double sigma = 0.0, c_scale = 0.0;
@@ -238,6 +238,8 @@ void layout(Job* jb) {
   const int64_t tiles = (N + 31) / 32;
   jb->chunk = serve_chunk(N);
   jb->nitems = (int)((tiles + jb->chunk - 1) / jb->chunk);
+  jb->unit = serve_unit(N);
+  jb->nunits = (jb->nitems + jb->unit - 1) / jb->unit;
   size_t o = 0;
   auto take = [&o](size_t bytes) {
     const size_t at = o;
@@ -285,10 +287,10 @@ hipError_t launch_batch(air_server* s, Slot& sl) {
   JobOut* ho = reinterpret_cast<JobOut*>(sl.h_block + kDescBytes);
   const JobDesc* dd = reinterpret_cast<const JobDesc*>(sl.d_block);
   JobOut* dout = reinterpret_cast<JobOut*>(sl.d_block + kDescBytes);
-  int64_t item0 = 0;
+  int64_t item0 = 0, unit0 = 0;
   for (int k = 0; k < n; ++k) {
     Job* jb = jobs[k];
-    if (k > 0 && jobs[k - 1]->cls != jb->cls) item0 = 0;
+    if (k > 0 && jobs[k - 1]->cls != jb->cls) item0 = unit0 = 0;
     char* base = s->arena_base + jb->off;
     const air_const* c = jb->c;
     const bool bf = jb->j.prec == AIR_BF16X3;
@@ -306,8 +308,10 @@ hipError_t launch_batch(air_server* s, Slot& sl) {
     d.out = dout + k;
     d.N = jb->j.N;
     d.item0 = item0;
+    d.unit0 = unit0;
     d.nitems = jb->nitems;
     d.chunk = jb->chunk;
+    d.unit = jb->unit;
     d.M = c->M;
     d.m = c->m;
     d.sweep = jb->j.noise_in ? 1 : 0;
@@ -315,6 +319,7 @@ hipError_t launch_batch(air_server* s, Slot& sl) {
     d.sigma = (float)jb->sigma;
     std::memset(&ho[k], 0, sizeof(JobOut));
     item0 += jb->nitems;
+    unit0 += jb->nunits;
   }
   const hipStream_t st = sl.stream;
   const uint64_t t_launch = now_ns();
@@ -330,14 +335,15 @@ hipError_t launch_batch(air_server* s, Slot& sl) {
   }
   // one launch per kernel class and tier
   for (int a = 0; a < n && e == hipSuccess;) {
-    int b = a + 1;
-    int64_t items = jobs[a]->nitems;
-    while (b < n && jobs[b]->cls == jobs[a]->cls) items += jobs[b++]->nitems;
+    int b;
+    int64_t items = 0, units = 0;
+    for (b = a; b < n && jobs[b]->cls == jobs[a]->cls; ++b) {
+      items += jobs[b]->nitems;
+      units += jobs[b]->nunits;
+    }
     const Job* ja = jobs[a];
     const ServeFn fn = ja->j.prec == AIR_BF16X3 ? kServeBF16[ja->c->D] : kServeF16[ja->c->D];
-    const int64_t g = (items + 3) / 4;
-    const int grid = (int)(g < kMaxClassGrid ? g : kMaxClassGrid);
-    e = fn(dd + a, b - a, items, ja->c->M == 16, grid, st);
+    e = fn(dd + a, b - a, items, units, ja->c->M == 16, kMaxClassGrid, st);
     a = b;
   }
   if (e == hipSuccess) {

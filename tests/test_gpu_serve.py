@@ -92,6 +92,27 @@ def test_serve_oracle_parity(ctx, consts, prec, M, D):
     assert_llr(L.cpu().numpy(), ref["llr"][0], LLR_BAR[prec])
 
 
+@pytest.mark.parametrize("snr", [16.0, 30.0])       # few flagged samples per tile; nearly all
+@pytest.mark.parametrize("N", [65504, 65505, 131073, 300001, 1048609])
+def test_serve_second_tier_gather(ctx, consts, N, snr):
+    """The second tier gathers flagged samples over runs of sample tiles: one
+    tile up to 65504 samples, two or more from there on, items of several
+    tiles above 131072 and more tiles than the gather queue holds above
+    1048576. Every LLR and the sums against the FP64 sweep."""
+    X, lab, c = consts[64]
+    tx, z = _block(64, 4, N, 17)
+    zd, td = to_dev(z), tx_dev(tx)
+    sv = ctx.server(1 << 30)
+    L = torch.full((N, c.m), float("nan"), device=ctx.torch_device)
+    r = _run_alone(sv, dict(c=c, inp=zd, tx=td, snr_db=snr, prec="fp16x3", noise=True, llr=L))
+    sv.close()
+    st, ref = ctx.sweep(c, td, zd.double(), [snr], prec="fp64", llr=True)
+    ctx.sync()
+    assert r["status"] == air.AIR_OK and r["recomputed"] > 0
+    assert_stats(np.array([_stats(r)]), st.cpu().numpy(), se_rel=2e-2)
+    assert_llr(L.cpu().numpy(), ref.cpu().numpy()[0], LLR_BAR["fp16x3"])
+
+
 @pytest.mark.parametrize("M,D", MIX)
 def test_serve_matches_one_shot(ctx, consts, M, D):
     """Same received block through air_mi_gmi and through the server. The
