@@ -25,19 +25,36 @@
 namespace air {
 
 // How the per-point values of a sample are combined: sums of the terms
-// 2^a_j (exact demapping), or maxima of the exponents a_j (max-log).
-template <bool ML>
+// 2^a_j (exact demapping), or maxima of the exponents a_j (max-log). fmax of a
+// value that comes from a product or a loop is preceded by a quieting of it,
+// which was half of the vector work of the maxima; the NaN-propagating maximum
+// needs none and takes three operands. It stands only where no exponent can be
+// NaN: in half precision every sample with an operand of 60000 or more (or
+// NaN) is marked and its sides are formed by maxlog_direct, so the exponents
+// of the others are finite. bfloat16 operands have no such mark and keep fmax.
+enum Combine { kSum = 0, kFmax = 1, kMaximum = 2 };
+template <bool BF, bool ML>
+constexpr int combine_of() { return ML ? (BF ? kFmax : kMaximum) : kSum; }
+template <int CM>
 __device__ __forceinline__ float cmb(float x, float y) {
-  if constexpr (ML) return __builtin_fmaxf(x, y);
+  if constexpr (CM == kMaximum) return __builtin_elementwise_maximum(x, y);
+  else if constexpr (CM == kFmax) return __builtin_fmaxf(x, y);
   else return x + y;
 }
+// Four values (maxima: in the order that folds into three-operand steps).
+template <int CM>
+__device__ __forceinline__ float cmb4(float a, float b, float c, float d) {
+  if constexpr (CM == kSum) return (a + b) + (c + d);
+  else return cmb<CM>(cmb<CM>(cmb<CM>(a, b), c), d);
+}
 
-// Running sums (maxima for ML) of one lane over the point tiles, with LV
-// tile levels. The two forms are written out separately: the sums' form is
-// kept exactly as the compiler handles it best (its level arrays stay in
-// registers in the run-time-M form).
-template <int NE, int LV, bool ML = false>
+// Running sums (maxima for max-log) of one lane over the point tiles, with LV
+// tile levels. add() is written out for the sums and the maxima separately: with
+// one text for both the compiler moves the sums' level arrays to scratch (16-D in
+// half precision 560 -> 650 us).
+template <int NE, int LV, int CM = kSum>
 struct WideSums {
+  static constexpr bool ML = CM != kSum;
   float R[NE];
   float g0[LV > 0 ? LV : 1], g1[LV > 0 ? LV : 1], gn[LV > 0 ? LV : 1];
   float tot;
@@ -48,30 +65,27 @@ struct WideSums {
     tot = z;
   }
   __device__ __forceinline__ void add(float (&ev)[NE], int t, int ntb) {
-    if constexpr (ML) {
-      // (in the run-time-M form the compiler keeps g0 / g1 of this form in
-      // scratch; an order-free update of every level per tile, which avoids
-      // that, measured slower)
+    if constexpr (CM != kSum) {
       if (t == 0) {
 #pragma unroll
         for (int e = 0; e < NE; ++e) R[e] = ev[e];
       } else {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) R[e] = __builtin_fmaxf(R[e], ev[e]);
+        for (int e = 0; e < NE; ++e) R[e] = cmb<CM>(R[e], ev[e]);
       }
 #pragma unroll
       for (int w2 = NE / 2; w2 >= 1; w2 >>= 1)
 #pragma unroll
-        for (int e = 0; e < w2; ++e) ev[e] = __builtin_fmaxf(ev[2 * e], ev[2 * e + 1]);
+        for (int e = 0; e < w2; ++e) ev[e] = cmb<CM>(ev[2 * e], ev[2 * e + 1]);
       float carry = ev[0];
       bool placed = false;
 #pragma unroll
       for (int l = 0; l < LV; ++l) {
         if (!placed && l < ntb) {
           if ((t >> l) & 1) {
-            g0[l] = __builtin_fmaxf(g0[l], gn[l]);
-            g1[l] = __builtin_fmaxf(g1[l], carry);
-            carry = __builtin_fmaxf(gn[l], carry);
+            g0[l] = cmb<CM>(g0[l], gn[l]);
+            g1[l] = cmb<CM>(g1[l], carry);
+            carry = cmb<CM>(gn[l], carry);
           } else {
             gn[l] = carry;
             placed = true;
@@ -109,25 +123,32 @@ struct WideSums {
       if (!placed) tot = carry;
     }
   }
-  // The run-time-M form of the sums takes four tiles at a time (M >= 128):
+  // The run-time-M form takes four tiles at a time (M >= 128):
   // tile() adds one tile's terms to R (zeroed first) and returns the tile's
   // total, quad() hands the four totals of tiles 4 q ... 4 q + 3 to the levels,
   // the two lowest in straight code, the others by the counter. Every sum is
   // formed in the order in which add() forms it.
   __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) R[e] = 0.f;
+    for (int e = 0; e < NE; ++e)
+      R[e] = CM == kSum ? 0.f : (CM == kMaximum ? -__builtin_inff() : __builtin_nanf(""));  // fmax(NaN, x) = x
   }
   __device__ __forceinline__ float tile(float (&ev)[NE]) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) R[e] += ev[e];
+    for (int e = 0; e < NE; ++e) R[e] = cmb<CM>(R[e], ev[e]);
     // the additions take place here (they would be moved behind the levels'
     // branches, with every tile's terms held until there)
     pin(R);
+    if constexpr (CM == kMaximum && NE == 16) {
+      auto m3 = [](float a, float b, float c) { return cmb<CM>(cmb<CM>(a, b), c); };
+      const float a = m3(ev[0], ev[1], ev[2]), b = m3(ev[3], ev[4], ev[5]), c = m3(ev[6], ev[7], ev[8]);
+      const float d = m3(ev[9], ev[10], ev[11]), e = m3(ev[12], ev[13], ev[14]);
+      return cmb<CM>(m3(m3(a, b, c), d, e), ev[15]);
+    }
 #pragma unroll
     for (int w2 = NE / 2; w2 >= 1; w2 >>= 1)
 #pragma unroll
-      for (int e = 0; e < w2; ++e) ev[e] = ev[2 * e] + ev[2 * e + 1];
+      for (int e = 0; e < w2; ++e) ev[e] = cmb<CM>(ev[2 * e], ev[2 * e + 1]);
     return ev[0];
   }
   // (both groups together: one set of branches)
@@ -147,12 +168,12 @@ struct WideSums {
     for (int l = 2; l < LV; ++l) {
       if (!placed && l < ntb) {
         if ((q >> (l - 2)) & 1) {
-          A.g0[l] += A.gn[l];
-          A.g1[l] += ca;
-          ca = A.gn[l] + ca;
-          B.g0[l] += B.gn[l];
-          B.g1[l] += cb;
-          cb = B.gn[l] + cb;
+          A.g0[l] = cmb<CM>(A.g0[l], A.gn[l]);
+          A.g1[l] = cmb<CM>(A.g1[l], ca);
+          ca = cmb<CM>(A.gn[l], ca);
+          B.g0[l] = cmb<CM>(B.g0[l], B.gn[l]);
+          B.g1[l] = cmb<CM>(B.g1[l], cb);
+          cb = cmb<CM>(B.gn[l], cb);
         } else {
           A.gn[l] = ca;
           B.gn[l] = cb;
@@ -166,12 +187,12 @@ struct WideSums {
     }
   }
   __device__ __forceinline__ void low2(const float (&c)[4], float& carry) {
-    g0[0] = (g0[0] + c[0]) + c[2];
-    g1[0] = (g1[0] + c[1]) + c[3];
-    const float p0 = c[0] + c[1], p1 = c[2] + c[3];
-    g0[1] += p0;
-    g1[1] += p1;
-    carry = p0 + p1;
+    g0[0] = cmb<CM>(cmb<CM>(g0[0], c[0]), c[2]);
+    g1[0] = cmb<CM>(cmb<CM>(g1[0], c[1]), c[3]);
+    const float p0 = cmb<CM>(c[0], c[1]), p1 = cmb<CM>(c[2], c[3]);
+    g0[1] = cmb<CM>(g0[1], p0);
+    g1[1] = cmb<CM>(g1[1], p1);
+    carry = cmb<CM>(p0, p1);
   }
 };
 
@@ -184,7 +205,7 @@ struct WideSums {
 // bit (label bit 5) come from the tiles' totals after the exchange between
 // the lane halves; with two tiles each tile's total is taken from its own
 // row sums (3 operations), with one tile from its sides.
-template <bool ML, int NT>
+template <int CM, int NT>
 struct TileMarg {
   float r[4], c[4];     // row and column sums over the tiles
   float tt[2];          // totals of tiles 0 and 1 (NT = 2)
@@ -192,10 +213,10 @@ struct TileMarg {
   __device__ __forceinline__ void add(const float (&ev)[16], int t) {
     float rr[4], cc[4];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) rr[x] = cmb<ML>(cmb<ML>(ev[4 * x], ev[4 * x + 1]), cmb<ML>(ev[4 * x + 2], ev[4 * x + 3]));
+    for (int x = 0; x < 4; ++x) rr[x] = cmb4<CM>(ev[4 * x], ev[4 * x + 1], ev[4 * x + 2], ev[4 * x + 3]);
 #pragma unroll
-    for (int y = 0; y < 4; ++y) cc[y] = cmb<ML>(cmb<ML>(ev[y], ev[4 + y]), cmb<ML>(ev[8 + y], ev[12 + y]));
-    if (NT == 2) tt[t] = cmb<ML>(cmb<ML>(rr[0], rr[1]), cmb<ML>(rr[2], rr[3]));
+    for (int y = 0; y < 4; ++y) cc[y] = cmb4<CM>(ev[y], ev[4 + y], ev[8 + y], ev[12 + y]);
+    if (NT == 2) tt[t] = cmb4<CM>(rr[0], rr[1], rr[2], rr[3]);
     if (t == 0) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -205,21 +226,21 @@ struct TileMarg {
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        r[i] = cmb<ML>(r[i], rr[i]);
-        c[i] = cmb<ML>(c[i], cc[i]);
+        r[i] = cmb<CM>(r[i], rr[i]);
+        c[i] = cmb<CM>(c[i], cc[i]);
       }
     }
   }
   __device__ __forceinline__ void finish() {
-    es[0] = cmb<ML>(c[0], c[2]);
-    es[1] = cmb<ML>(c[1], c[3]);
-    es[2] = cmb<ML>(c[0], c[1]);
-    es[3] = cmb<ML>(c[2], c[3]);
-    es[4] = cmb<ML>(r[0], r[2]);
-    es[5] = cmb<ML>(r[1], r[3]);
-    es[6] = cmb<ML>(r[0], r[1]);
-    es[7] = cmb<ML>(r[2], r[3]);
-    if (NT == 1) tt[0] = cmb<ML>(es[6], es[7]);
+    es[0] = cmb<CM>(c[0], c[2]);
+    es[1] = cmb<CM>(c[1], c[3]);
+    es[2] = cmb<CM>(c[0], c[1]);
+    es[3] = cmb<CM>(c[2], c[3]);
+    es[4] = cmb<CM>(r[0], r[2]);
+    es[5] = cmb<CM>(r[1], r[3]);
+    es[6] = cmb<CM>(r[0], r[1]);
+    es[7] = cmb<CM>(r[2], r[3]);
+    if (NT == 1) tt[0] = cmb<CM>(es[6], es[7]);
   }
 };
 
@@ -470,9 +491,14 @@ __device__ __forceinline__ float softplus2(float x) {
 // slots and 31 additions per 16 points). 12-D/4096 rates (N = 1.6e7, 41 SNR
 // points) 427 -> 354 ms, 8-D/2048 first tier 13.2 -> 10.6 ms; M = 128 1.03x,
 // M = 512 1.13x. The four-chunk half-precision form (D = 16) spills with it
-// and measured 0.94-0.98x: it keeps the plain loop.
+// and measured 0.94-0.98x: it keeps the plain loop. Max-log takes the elements
+// themselves, without a copy, and always gains (half precision, 1.5e6 samples
+// at two SNR points with LLRs: 4-D/128 141 -> 101 us, 8-D/2048 1141 -> 583,
+// 12-D/2048 1203 -> 723, 16-D/2048 2259 -> 1478; bfloat16 with its fmax 1.05-1.56x),
+// but for 16-D/128 in bfloat16 (190 -> 196); one record set above 8 dimensions,
+// two spill there (12-D/128 0.75x).
 template <int D, bool BF>
-constexpr bool w_pipe(int MB, bool ML) { return MB == 0 && !ML && (BF || mfma_nk(D, BF) <= 3); }
+constexpr bool w_pipe(int MB, bool ML) { return MB == 0 && (ML || BF || mfma_nk(D, BF) <= 3); }
 
 // ML: the max-log form. Each bit side keeps the largest exponent instead of
 // the sum of the terms; the LLR is ln 2 times the difference of the two
@@ -480,13 +506,16 @@ constexpr bool w_pipe(int MB, bool ML) { return MB == 0 && !ML && (BF || mfma_nk
 // sum_k log2(1 + 2^(-(1 - 2 b_k) L_k / ln 2)); the transmitted point's own
 // term, the logarithms of the sums and the second tier are not needed (no
 // sum can starve). Samples whose operands leave the operand range are done
-// by maxlog_direct.
+// by maxlog_direct. Bound by vector issue (the maxima and the LLRs' stores):
+// 8-PSK x 8-PSK, 1e6 samples, 21 SNR points with LLRs 238 -> 198 us with the
+// three-operand maximum (cmb); writing the LLRs alone takes 99 us.
 template <int D, bool BF, bool TBL, int MB, bool ML = false>
 __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>(MB, ML) ? 2 : 1)) void demap_mfma_w(const DemapArgs a,
                                                     const typename MfmaOp<BF>::vec* __restrict__ rec,
                                                     const float* __restrict__ xl) {
   typedef typename MfmaOp<BF>::vec V;
   typedef WideOperand<D, BF> OP;
+  constexpr int CM = combine_of<BF, ML>();
   constexpr bool HALF = MB == 4;                                   // 16-point tiles
   constexpr int LV = MB == 0 ? kTileLevels : (MB > 5 ? MB - 5 : 0);  // tile levels carried
   constexpr int NK = OP::NK;
@@ -509,7 +538,7 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
   // products a tile ahead (w_pipe); two sets of point records in registers
   // where they fit into 256 with the rest
   constexpr bool PIPE = w_pipe<D, BF>(MB, ML);
-  constexpr int NSET = D <= 12 ? 2 : 1;
+  constexpr int NSET = D <= (ML ? 8 : 12) ? 2 : 1;
   extern __shared__ double acc_lds[];      // [waves][s_per][4], then the tables (TBL)
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
@@ -632,8 +661,8 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
         arg_t = hj ? hi : lo;
       }
 
-      WideSums<NE, LV, ML> sA, sB;
-      TileMarg<ML, (MB == 6 ? 2 : 1)> mA, mB;
+      WideSums<NE, LV, CM> sA, sB;
+      TileMarg<CM, (MB == 6 ? 2 : 1)> mA, mB;
       if constexpr (!MARG) {
         sA.init();
         sB.init();
@@ -663,21 +692,25 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
             V (&A)[NK] = rs[(u + 1) & (NSET - 1)];
             float ev[NE];
 #pragma unroll
-            for (int e = 0; e < NE; ++e) ev[e] = Real<float>::exp2(accA[e]);
+            for (int e = 0; e < NE; ++e) ev[e] = ML ? accA[e] : Real<float>::exp2(accA[e]);
+            // (maxima: the elements themselves, taken before their registers
+            // are written again; the other group's product is in flight)
+            if constexpr (ML) cA[u] = sA.tile(ev);
             accA = opA.product(A);
-            cA[u] = sA.tile(ev);
+            if constexpr (!ML) cA[u] = sA.tile(ev);
             // one group's terms in registers at a time
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < NE; ++e) ev[e] = Real<float>::exp2(accB[e]);
+            for (int e = 0; e < NE; ++e) ev[e] = ML ? accB[e] : Real<float>::exp2(accB[e]);
+            if constexpr (ML) cB[u] = sB.tile(ev);
             accB = opB.product(A);
             load(A, (t + u + 1 + NSET) & (NT - 1));
             // keeps the loads here (else merged into loads before their use)
             asm volatile("" ::: "memory");
-            cB[u] = sB.tile(ev);
+            if constexpr (!ML) cB[u] = sB.tile(ev);
             __builtin_amdgcn_sched_barrier(0);
           }
-          WideSums<NE, LV, ML>::quad(sA, sB, cA, cB, t >> 2, ntb);
+          WideSums<NE, LV, CM>::quad(sA, sB, cA, cB, t >> 2, ntb);
         }
       } else {
         V A[NK];
@@ -723,22 +756,22 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
           float lo, hi;
           own_halves(mA.es[i], mB.es[i], lo, hi);
           const int eb = i >> 1;
-          side[2 * (eb < 2 ? eb : eb + 1) + (i & 1)] = cmb<ML>(lo, hi);
+          side[2 * (eb < 2 ? eb : eb + 1) + (i & 1)] = cmb<CM>(lo, hi);
         }
         float t0lo, t0hi;
         own_halves(mA.tt[0], mB.tt[0], t0lo, t0hi);
         if constexpr (MB == 6) {
           float t1lo, t1hi;
           own_halves(mA.tt[1], mB.tt[1], t1lo, t1hi);
-          side[10] = cmb<ML>(t0lo, t0hi);      // label bit 5: the tile
-          side[11] = cmb<ML>(t1lo, t1hi);
-          side[4] = cmb<ML>(t0lo, t1lo);       // label bit 2: the lane half
-          side[5] = cmb<ML>(t0hi, t1hi);
-          total = cmb<ML>(side[10], side[11]);
+          side[10] = cmb<CM>(t0lo, t0hi);      // label bit 5: the tile
+          side[11] = cmb<CM>(t1lo, t1hi);
+          side[4] = cmb<CM>(t0lo, t1lo);       // label bit 2: the lane half
+          side[5] = cmb<CM>(t0hi, t1hi);
+          total = cmb<CM>(side[10], side[11]);
         } else {
           side[4] = t0lo;
           side[5] = t0hi;
-          total = cmb<ML>(t0lo, t0hi);
+          total = cmb<CM>(t0lo, t0hi);
         }
       } else {
         // both row halves of the own sample
@@ -748,24 +781,24 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
         {
           float t0, t1;
           own_halves(sA.tot, sB.tot, t0, t1);
-          total = cmb<ML>(t0, t1);
+          total = cmb<CM>(t0, t1);
         }
 #pragma unroll
         for (int l = 0; l < LV; ++l)
           if (l < ntb) {
             float x0, x1;
             own_halves(sA.g0[l], sB.g0[l], x0, x1);
-            side[2 * (5 + l)] = cmb<ML>(x0, x1);
+            side[2 * (5 + l)] = cmb<CM>(x0, x1);
             own_halves(sA.g1[l], sB.g1[l], x0, x1);
-            side[2 * (5 + l) + 1] = cmb<ML>(x0, x1);
+            side[2 * (5 + l) + 1] = cmb<CM>(x0, x1);
           }
         {
           // label bit 2 is the row half
           float c0 = r0[0], c1 = r1[0];
 #pragma unroll
           for (int e = 1; e < NE; ++e) {
-            c0 = cmb<ML>(c0, r0[e]);
-            c1 = cmb<ML>(c1, r1[e]);
+            c0 = cmb<CM>(c0, r0[e]);
+            c1 = cmb<CM>(c1, r1[e]);
           }
           side[4] = c0;
           side[5] = c1;
@@ -774,7 +807,7 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
           // label bits 0, 1, 3 (, 4) are the element bits 0, 1, 2 (, 3)
           float cur[NE];
 #pragma unroll
-          for (int e = 0; e < NE; ++e) cur[e] = cmb<ML>(r0[e], r1[e]);
+          for (int e = 0; e < NE; ++e) cur[e] = cmb<CM>(r0[e], r1[e]);
 #pragma unroll
           for (int eb = 0; eb < NEB; ++eb) {
             const int half = NE >> (eb + 1);
@@ -782,12 +815,12 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
 #pragma unroll
             for (int i = 1; i < NE / 2; ++i)
               if (i < half) {
-                a0 = cmb<ML>(a0, cur[2 * i]);
-                a1 = cmb<ML>(a1, cur[2 * i + 1]);
+                a0 = cmb<CM>(a0, cur[2 * i]);
+                a1 = cmb<CM>(a1, cur[2 * i + 1]);
               }
 #pragma unroll
             for (int i = 0; i < NE / 2; ++i)
-              if (i < half) cur[i] = cmb<ML>(cur[2 * i], cur[2 * i + 1]);
+              if (i < half) cur[i] = cmb<CM>(cur[2 * i], cur[2 * i + 1]);
             const int k = eb < 2 ? eb : eb + 1;
             side[2 * k] = a0;
             side[2 * k + 1] = a1;

@@ -102,6 +102,33 @@ def test_maxlog_operands_out_of_range_fall_back(ctx):
     c.close()
 
 
+@pytest.mark.parametrize("prec", ["fp16x3", "bf16x3"])
+@pytest.mark.parametrize("M,D", [(64, 4), (128, 2), (128, 8), (512, 9), (2048, 12), (4096, 16)])
+def test_maxlog_stray_samples(ctx, M, D, prec):
+    """Samples that are NaN, infinite or huge leave every other sample's LLRs
+    as they are (bitwise), NaN gives NaN LLRs, and the point loop of four tiles
+    per step matches the oracle on the others."""
+    N, snr_db = 333, 9.0
+    X, lab = inputs.random_constellation(M + 7 * D, M, D)
+    tx, z = inputs.random_block(M + D, M, N, D)
+    Y = (X[tx] + math.sqrt(oracle.sigma2(X, snr_db)) * z.astype(np.float64)).astype(np.float32)
+    c = ctx.const(X, lab)
+    _, clean = ctx.gmi_maxlog(c, to_dev(Y), tx_dev(tx), snr_db, prec, llr=True)
+    ref = oracle.evaluate_maxlog(X, lab, Y.astype(np.float64), snr_db, tx=tx)
+    assert_llr(clean.cpu().numpy(), ref["llr"], rel=LLR_BAR[prec])
+    stray = {5: np.nan, 40: np.inf, 170: -np.inf, 332: 1e30}
+    Yb = Y.copy()
+    for i, x in stray.items():
+        Yb[i, 0] = x
+    _, L = ctx.gmi_maxlog(c, to_dev(Yb), tx_dev(tx), snr_db, prec, llr=True)
+    ctx.sync()
+    keep = torch.ones(N, dtype=torch.bool, device=L.device)
+    keep[list(stray)] = False
+    assert torch.equal(L[keep], clean[keep])
+    assert torch.isnan(L[5]).all()
+    c.close()
+
+
 def test_maxlog_invalid_tx(ctx):
     X, lab = inputs.random_constellation(77, 64, 4)
     tx, z = inputs.random_block(78, 64, 500, 4)
