@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ 
     return t;
   });
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (bad) atomicOr(f.sticky, bad);
+    if (bad) flag_sticky(f.sticky);
     clear_call_words(f.next);
   }
 }
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const double* __restrict__ 
 // call's words (calls without a reduction kernel of their own).
 __global__ void fold_error_kernel(const CallWords* call, CallWords* next, int* sticky) {
   if (threadIdx.x == 0) {
-    if (call->err) atomicOr(sticky, call->err);
+    if (call->err) flag_sticky(sticky);
     clear_call_words(next);
   }
 }
@@ -357,7 +357,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   if (!g.ok) return fail(ctx, AIR_E_DEVICE, "cannot select the context's device");
   if (!is_device_ptr(ctx, in)) return fail(ctx, AIR_E_INVAL, "input block is not device memory of this context");
   if (tx && !is_device_ptr(ctx, tx)) return fail(ctx, AIR_E_INVAL, "tx_dev is not device memory of this context");
-  if (stats && !is_device_ptr(ctx, stats)) return fail(ctx, AIR_E_INVAL, "stats_dev is not device memory of this context");
+  if (stats && stats != ctx->small + (kMaxD + 1) && !is_device_ptr(ctx, stats)) return fail(ctx, AIR_E_INVAL, "stats_dev is not device memory of this context");
   if (llr && !is_device_ptr(ctx, llr)) return fail(ctx, AIR_E_INVAL, "llr_dev is not device memory of this context");
 
   const bool fp64 = prec == AIR_FP64;
@@ -587,7 +587,7 @@ air_status run_noise_var(air_ctx* ctx, const air_const* c, const void* Y, const 
   if (!g.ok) return fail(ctx, AIR_E_DEVICE, "cannot select the context's device");
   if (!is_device_ptr(ctx, Y)) return fail(ctx, AIR_E_INVAL, "Y_dev is not device memory of this context");
   if (!is_device_ptr(ctx, tx)) return fail(ctx, AIR_E_INVAL, "tx_dev is not device memory of this context");
-  if (!is_device_ptr(ctx, var)) return fail(ctx, AIR_E_INVAL, "var_dev is not device memory of this context");
+  if (var != ctx->small && !is_device_ptr(ctx, var)) return fail(ctx, AIR_E_INVAL, "var_dev is not device memory of this context");
   CallWords* next = nullptr;
   hipError_t e = begin_call(ctx, &next);
   if (e != hipSuccess) return hip_fail(ctx, e, "clear call words");
@@ -630,13 +630,13 @@ air_status air_create(air_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipMalloc(&ctx->t2_partials, sizeof(double) * kMaxGrid * kMaxSnrPerLaunch * 4);
     if (e == hipSuccess) e = hipMalloc(&ctx->t2_tot, sizeof(unsigned int) * kMaxSnrPerLaunch);
     if (e == hipSuccess) e = hipMalloc(&ctx->calls, 2 * sizeof(CallWords));
-    if (e == hipSuccess) e = hipMalloc(&ctx->sticky, sizeof(int));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->sticky, sizeof(int), hipHostMallocDefault);
     if (e == hipSuccess) e = hipMalloc(&ctx->ticket, sizeof(unsigned int));
     if (e == hipSuccess) e = hipMemset(ctx->ticket, 0, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipMalloc(&ctx->small, sizeof(double) * kSmallDoubles);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->small, sizeof(double) * kSmallDoubles, hipHostMallocDefault);
     if (e == hipSuccess) e = hipMemset(ctx->calls, 0, 2 * sizeof(CallWords));
     ctx->call = ctx->calls;
-    if (e == hipSuccess) e = hipMemset(ctx->sticky, 0, sizeof(int));
+    if (e == hipSuccess) *ctx->sticky = 0;
     if (e == hipSuccess) e = hipDeviceSynchronize();
     // the no-allocation entry point's scratch on this device (looked up once
     // per device; if that fails, air_sweep_noalloc reports it)
@@ -658,12 +658,12 @@ void air_destroy(air_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   (void)hipFree(ctx->partials);
   (void)hipFree(ctx->calls);
-  (void)hipFree(ctx->sticky);
+  if (ctx->sticky) (void)hipHostFree(ctx->sticky);
   (void)hipFree(ctx->ticket);
   free_t2(ctx);
   (void)hipFree(ctx->t2_partials);
   (void)hipFree(ctx->t2_tot);
-  (void)hipFree(ctx->small);
+  if (ctx->small) (void)hipHostFree(ctx->small);
   for (hipEvent_t ev : ctx->ev) (void)hipEventDestroy(ev);
   delete ctx;
 }
@@ -688,13 +688,9 @@ air_status air_sync(air_ctx* ctx) {
     DeviceGuard g(ctx->device);
     hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "stream synchronize");
-    int sticky = 0;
-    e = hipMemcpy(&sticky, ctx->sticky, sizeof(int), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(ctx, e, "read device error word");
-    if (sticky) {
-      const int zero = 0;
-      e = hipMemcpy(ctx->sticky, &zero, sizeof(int), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(ctx, e, "clear device error word");
+    volatile int* sticky = ctx->sticky;   // written by the kernels that have ended
+    if (*sticky) {
+      *sticky = 0;
       return fail(ctx, AIR_E_RANGE, "a transmitted index >= M was seen; affected statistics are NaN");
     }
     return AIR_OK;
@@ -855,16 +851,16 @@ air_status air_aux_rates(air_ctx* ctx, const air_const* c, const void* Y_dev, co
     if (!ctx) return AIR_E_INVAL;
     if (!c || c->ctx != ctx) return fail(ctx, AIR_E_INVAL, "constellation is null or from another context");
     static_assert(kMaxD + 1 + 4 <= kSmallDoubles, "small device buffer too small");
-    double* var_dev = ctx->small;
-    double* stats_dev = ctx->small + (kMaxD + 1);
-    air_status st = run_noise_var(ctx, c, Y_dev, tx_dev, N, prec, var_dev);
+    double* const own_var = ctx->small;
+    double* const own_stats = ctx->small + (kMaxD + 1);
+    air_status st = run_noise_var(ctx, c, Y_dev, tx_dev, N, prec, own_var);
     if (st != AIR_OK) return st;
     DeviceGuard g(ctx->device);
     double var[kMaxD + 1];
     // the estimate is needed on the host to form the metric's scale
-    hipError_t e = hipMemcpyAsync(var, var_dev, sizeof(double) * (c->D + 1), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "read the noise estimate");
+    std::memcpy(var, own_var, sizeof(double) * (c->D + 1));
     if (var_host)
       for (int d = 0; d <= c->D; ++d) var_host[d] = var[d];
     const double s2 = var[c->D];
@@ -874,12 +870,12 @@ air_status air_aux_rates(air_ctx* ctx, const air_const* c, const void* Y_dev, co
       const air_status se = air_sync(ctx);   // reports a tx-range error
       return se != AIR_OK ? se : fail(ctx, AIR_E_RANGE, "noise estimate is zero or not finite");
     }
-    st = run(ctx, c, Y_dev, tx_dev, N, &s2, 1, 0, prec, stats_dev, nullptr, true);
+    st = run(ctx, c, Y_dev, tx_dev, N, &s2, 1, 0, prec, own_stats, nullptr, true);
     if (st != AIR_OK) return st;
     double stats[4];
-    e = hipMemcpyAsync(stats, stats_dev, sizeof(stats), hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "read the rates");
+    std::memcpy(stats, own_stats, sizeof(stats));
     rates_host[0] = s2;
     for (int i = 0; i < 4; ++i) rates_host[1 + i] = stats[i];
     st = air_ngmi(stats, 1, c->m, rates_host + 5);

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64 * kMaxD) void noise_var_finish(const double* __r
     double all = 0.0;
     for (int k = 0; k < D; ++k) all += each[k];
     var[D] = bad ? __builtin_nan("") : all / (double)D;
-    if (bad) atomicOr(sticky, 1);
+    if (bad) flag_sticky(sticky);
     clear_call_words(next);
   }
 }

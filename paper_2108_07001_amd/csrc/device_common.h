@@ -46,6 +46,12 @@ inline void launch_kernel(const Launch& l, F kernel, dim3 grid, dim3 block, uint
 
 // Per-call device words: the tx-range error of a call and the number of items
 // sent through the exact path; zero when the call starts.
+// Sets the context's error flag, which the host reads (host memory: a plain
+// store; every writer stores the same value).
+__device__ __forceinline__ void flag_sticky(int* sticky) {
+  __hip_atomic_store(sticky, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct CallWords {
   int err;
   int pad;

@@ -84,7 +84,7 @@ __device__ __forceinline__ void finish_in_last_block(const DemapArgs& a, int nbl
         return t;
       });
   if (threadIdx.x == 0) {
-    if (bad) atomicOr(a.fin.sticky, 1);
+    if (bad) flag_sticky(a.fin.sticky);
     clear_call_words(a.fin.next);
   }
 }
