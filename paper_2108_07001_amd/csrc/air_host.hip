@@ -629,14 +629,18 @@ air_status air_create(air_ctx** out, int device, void* hip_stream) {
     hipError_t e = hipMalloc(&ctx->partials, sizeof(double) * kMaxGrid * kMaxSnrPerLaunch * 4);
     if (e == hipSuccess) e = hipMalloc(&ctx->t2_partials, sizeof(double) * kMaxGrid * kMaxSnrPerLaunch * 4);
     if (e == hipSuccess) e = hipMalloc(&ctx->t2_tot, sizeof(unsigned int) * kMaxSnrPerLaunch);
-    if (e == hipSuccess) e = hipMalloc(&ctx->calls, 2 * sizeof(CallWords));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->sticky, sizeof(int), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMalloc(&ctx->ticket, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipMemset(ctx->ticket, 0, sizeof(unsigned int));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->small, sizeof(double) * kSmallDoubles, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMemset(ctx->calls, 0, 2 * sizeof(CallWords));
-    ctx->call = ctx->calls;
-    if (e == hipSuccess) *ctx->sticky = 0;
+    // call words and the ticket, and the host-readable words: one allocation each
+    constexpr size_t kWordBytes = 2 * sizeof(CallWords) + sizeof(unsigned int);
+    if (e == hipSuccess) e = hipMalloc(&ctx->calls, kWordBytes);
+    if (e == hipSuccess) e = hipMemset(ctx->calls, 0, kWordBytes);
+    if (e == hipSuccess)
+      e = hipHostMalloc((void**)&ctx->small, sizeof(double) * kSmallDoubles + sizeof(int), hipHostMallocDefault);
+    if (e == hipSuccess) {
+      ctx->call = ctx->calls;
+      ctx->ticket = reinterpret_cast<unsigned int*>(ctx->calls + 2);
+      ctx->sticky = reinterpret_cast<int*>(ctx->small + kSmallDoubles);
+      *ctx->sticky = 0;
+    }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     // the no-allocation entry point's scratch on this device (looked up once
     // per device; if that fails, air_sweep_noalloc reports it)
@@ -658,8 +662,6 @@ void air_destroy(air_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   (void)hipFree(ctx->partials);
   (void)hipFree(ctx->calls);
-  if (ctx->sticky) (void)hipHostFree(ctx->sticky);
-  (void)hipFree(ctx->ticket);
   free_t2(ctx);
   (void)hipFree(ctx->t2_partials);
   (void)hipFree(ctx->t2_tot);

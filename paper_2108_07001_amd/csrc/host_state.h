@@ -28,10 +28,10 @@ struct air_ctx {
   air::CallWords* calls = nullptr;
   air::CallWords* call = nullptr;  // the slot of the current (or last) call
   bool next_zeroed = true;         // the other slot is known to hold zeros
-  // pinned host memory that the kernels write: a tx-range error seen since the
-  // last air_sync
+  // pinned host memory that the kernels write (behind small): a tx-range error
+  // seen since the last air_sync
   int* sticky = nullptr;
-  unsigned int* ticket = nullptr;  // blocks done of the launch in flight (tail.h)
+  unsigned int* ticket = nullptr;  // blocks done of the launch in flight (tail.h); behind calls
   // second tier of the matrix-core path: per-wave tile lists and their counts
   unsigned long long* t2_list = nullptr;
   double* t2_partials = nullptr; // kMaxSnrPerLaunch x 4 x kMaxGrid
