@@ -534,9 +534,9 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
   // forming them here (at high SNR nearly every sample of a large set has a
   // bit side below the FP32 frame, and the first tier's work on it is lost)
   constexpr bool DIRECT = MB == 0 && !ML;
-  // run-time-M forms of the sums: four tiles per step of the point loop, the
-  // products a tile ahead (w_pipe); two sets of point records in registers
-  // where they fit into 256 with the rest
+  // run-time-M forms: four tiles per step of the point loop, the products a
+  // tile ahead (w_pipe); two sets of point records in registers where they fit
+  // into 256 with the rest
   constexpr bool PIPE = w_pipe<D, BF>(MB, ML);
   constexpr int NSET = D <= (ML ? 8 : 12) ? 2 : 1;
   extern __shared__ double acc_lds[];      // [waves][s_per][4], then the tables (TBL)
