@@ -406,50 +406,204 @@ __device__ __forceinline__ double log2_wide(double x) {
   return (double)e + (double)__builtin_amdgcn_logf((float)mant);
 }
 
-// Outputs of one FP32-family item from sums in the FP64 frame 2^(a + K64)
-// (the second tiers), this lane's own. Entries below thr64 are recomputed
-// exactly relative to the nearest point r and put back in the frame by
+// ---- the second tiers' exact path ------------------------------------------
+// Outputs of FP32-family items from sums in the FP64 frame 2^(a + K64) whose
+// entries fall below the bound thr64 of that frame. Those entries are
+// recomputed relative to the nearest point r and put back in the frame by
 // adding K64 + a_r; if the total itself is below thr64 every entry is
 // recomputed and all stay relative to a_r. lt_t is log2 of the transmitted
 // point's own term in the frame (used when tl >= 0 and the total is not
-// recomputed). Only the starved entries cost a pass over the constellation.
-// The caller counts the item (it is one of the second tier's items).
+// recomputed). The caller counts the items.
+//
+// Two forms: one item per lane, or one item after another by the whole wave,
+// which shares each pass over the points. The bits of an item do not depend on
+// the other items of its wave: sets of up to 2^NB points have both forms, which
+// add a sum's terms in the same order (a tree over each run of 16 labels, then
+// the runs in turn), and larger sets are always finished by the wave, whose
+// lanes add their own points' terms first. (With the form chosen by the number
+// of items alone, and a serial sum in one of them, an item's last bits changed
+// with the company it was listed in.)
+
+// -c times it: a_j - a_r, with its relative accuracy (rel_metric).
 template <int D>
-__device__ __forceinline__ void finish_item_frame64(const ExactArgs<float>& a, int64_t n, int tl, double total,
-                                                    const double (&side)[2 * kMaxBits], double thr64, int K64,
-                                                    double lt_t, float* llr_out, float& u, float& v) {
-  const int m = a.m;
-  float y[D];
-  reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, n, tl, y);
-  const int r = slow_nearest<float, D>(y, a.xl, a.M);
-  const bool total_slow = !(total >= thr64);
-  const double base =
-      total_slow ? 0.0 : (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
-  const uint32_t redo = exact_entries<double>(total, side, m, thr64);
-  double lam_tot = log2_wide(total);
-  double mem[2 * kMaxBits];      // logarithms of the recomputed entries; entry -1: the total
-#pragma unroll 1
-  for (int i = total_slow ? -1 : 0; i < 2 * m; ++i)
-    if (i < 0 || ((redo >> i) & 1u)) {
-      const double lam = base + (double)slow_rel<float, D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1);
-      if (i < 0) lam_tot = lam;
-      else mem[i] = lam;
-    }
+__device__ __forceinline__ float rel_dot(const float (&y)[D], const float (&xr)[D], const float* __restrict__ xj) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int d = 0; d < D; ++d) acc = __builtin_fmaf(xr[d] - xj[d], (y[d] - xr[d]) + (y[d] - xj[d]), acc);
+  return acc;
+}
+
+// u, v and the LLRs from the recomputed logarithms: lam[i] where bit i of
+// redo is set, the frame's own sums elsewhere. NB: the most bits of a label.
+template <int NB>
+__device__ __forceinline__ void finish_frame64_outputs(int m, int tl, uint32_t redo, const double (&side)[2 * kMaxBits],
+                                                       const double (&lam)[2 * NB], double lam_tot, double arg_t,
+                                                       float* llr_out, float& u, float& v) {
   double acc = 0.0;
 #pragma unroll
-  for (int k = 0; k < kMaxBits; ++k)
+  for (int k = 0; k < NB; ++k)
     if (k < m) {
-      const double l0 = ((redo >> (2 * k)) & 1u) ? mem[2 * k] : log2_wide(side[2 * k]);
-      const double l1 = ((redo >> (2 * k + 1)) & 1u) ? mem[2 * k + 1] : log2_wide(side[2 * k + 1]);
+      const double l0 = ((redo >> (2 * k)) & 1u) ? lam[2 * k] : log2_wide(side[2 * k]);
+      const double l1 = ((redo >> (2 * k + 1)) & 1u) ? lam[2 * k + 1] : log2_wide(side[2 * k + 1]);
       if (llr_out) llr_out[k] = (float)(0.6931471805599453094 * (l0 - l1));
       acc += lam_tot - (((tl >> k) & 1) ? l1 : l0);
     }
   if (tl >= 0) {
-    const double delta_t =
-        total_slow ? (double)rel_metric<float, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)tl * D, a.c) : lt_t;
-    u = (float)(lam_tot - delta_t);
+    u = (float)(lam_tot - arg_t);
     v = (float)acc;
   }
+}
+
+// Pairs, quads, eights, ... of e[0 .. N).
+template <int N>
+__device__ __forceinline__ float run_sum(float (&e)[N]) {
+#pragma unroll
+  for (int w = N / 2; w >= 1; w >>= 1)
+#pragma unroll
+    for (int i = 0; i < w; ++i) e[i] = e[2 * i] + e[2 * i + 1];
+  return e[0];
+}
+
+// As slow_rel, one bit side (k, b) of a lane's item.
+template <int D>
+__device__ __forceinline__ float lane_rel(const float (&y)[D], const float (&xr)[D], const float* __restrict__ xl,
+                                          int M, float c, int k, int b) {
+  const int lowmask = (1 << k) - 1;
+  auto label = [&](int i) { return ((i & ~lowmask) << 1) | (b << k) | (i & lowmask); };
+  const int cnt = M >> 1;
+  float dmax = -__builtin_inff(), sum = 0.0f;
+#pragma unroll 4
+  for (int i = 0; i < cnt; ++i) dmax = __builtin_fmaxf(dmax, -c * rel_dot<D>(y, xr, xl + (int64_t)label(i) * D));
+  // eight of the side's labels are a run's (k < 4) or half of one's
+  float half = 0.0f;
+  for (int i0 = 0; i0 < cnt; i0 += 8) {
+    float e[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      e[i] = i0 + i < cnt ? Real<float>::exp2(__builtin_fmaf(
+                                -c, rel_dot<D>(y, xr, xl + (int64_t)label(i0 + i < cnt ? i0 + i : 0) * D), -dmax))
+                          : 0.0f;
+    const float t = run_sum(e);
+    if (k < 4) sum += t;
+    else if (i0 & 8) sum += half + t;
+    else half = t;
+  }
+  return dmax + Real<float>::log2(sum);
+}
+
+// This lane's item (sets of at most 2^NB points). Where the lanes' items have
+// many starved sides together, one pass over the points takes the maxima of
+// all sides and one the sums; with few, each side takes its own two passes over
+// its half of the points.
+template <int D, int NB>
+__device__ __forceinline__ void finish_item_frame64(const ExactArgs<float>& a, int64_t n, int tl, double total,
+                                                    const double (&side)[2 * kMaxBits], double thr64, int K64,
+                                                    double lt_t, float* llr_out, float& u, float& v) {
+  const int m = a.m;
+  const float c = a.c;
+  float y[D];
+  reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, n, tl, y);
+  const int r = slow_nearest<float, D>(y, a.xl, a.M);
+  float xr[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) xr[d] = a.xl[(int64_t)r * D + d];
+  const bool total_slow = !(total >= thr64);
+  const double base = total_slow ? 0.0 : (double)K64 - (double)c * (double)sqdist<float, D>(y, xr);
+  const uint32_t redo = exact_entries<double>(total, side, m, thr64);
+  // the sides that are starved in any lane here, and whether a total is
+  uint32_t sides = 0u;
+#pragma unroll
+  for (int i = 0; i < 2 * NB; ++i) sides |= __ballot((redo >> i) & 1u) != 0ull ? 1u << i : 0u;
+  const bool totals = __ballot(total_slow) != 0ull;
+  float rel[2 * NB], rel_tot = 0.0f;
+  if (totals || __builtin_popcount(sides) * (3 * D + 4) > 6 * D + 8 * NB) {
+    constexpr int LB = NB < 4 ? NB : 4;
+    constexpr int G = 1 << LB;         // points at a time: a run
+    float mx[2 * NB], sm[2 * NB], mx_tot = -__builtin_inff(), sm_tot = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) {
+      mx[i] = -__builtin_inff();
+      sm[i] = 0.0f;
+    }
+#pragma unroll 1
+    for (int g = 0; g < a.M; g += G) {
+      float dj[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) dj[i] = -c * rel_dot<D>(y, xr, a.xl + (int64_t)(g + i) * D);
+#pragma unroll
+      for (int i = 0; i < G; ++i) mx_tot = __builtin_fmaxf(mx_tot, dj[i]);
+#pragma unroll
+      for (int k = 0; k < LB; ++k)
+#pragma unroll
+        for (int i = 0; i < G; ++i) mx[2 * k + ((i >> k) & 1)] = __builtin_fmaxf(mx[2 * k + ((i >> k) & 1)], dj[i]);
+#pragma unroll
+      for (int k = LB; k < NB; ++k) {
+        const bool one = (g >> k) & 1;
+        float cur = one ? mx[2 * k + 1] : mx[2 * k];
+#pragma unroll
+        for (int i = 0; i < G; ++i) cur = __builtin_fmaxf(cur, dj[i]);
+        mx[2 * k] = one ? mx[2 * k] : cur;
+        mx[2 * k + 1] = one ? cur : mx[2 * k + 1];
+      }
+    }
+#pragma unroll 1
+    for (int g = 0; g < a.M; g += G) {
+      float dot[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) dot[i] = rel_dot<D>(y, xr, a.xl + (int64_t)(g + i) * D);
+      auto term = [&](int i, float top) { return Real<float>::exp2(__builtin_fmaf(-c, dot[i], -top)); };
+#pragma unroll
+      for (int k = 0; k < LB; ++k)
+        if ((sides >> (2 * k)) & 3u) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float e[G / 2];
+#pragma unroll
+            for (int i = 0; i < G / 2; ++i)
+              e[i] = term(((i >> k) << (k + 1)) | (b << k) | (i & ((1 << k) - 1)), mx[2 * k + b]);
+            sm[2 * k + b] += run_sum(e);
+          }
+        }
+#pragma unroll
+      for (int k = LB; k < NB; ++k)
+        if ((sides >> (2 * k + ((g >> k) & 1))) & 1u) {
+          const bool one = (g >> k) & 1;
+          const float top = one ? mx[2 * k + 1] : mx[2 * k];
+          float e[G];
+#pragma unroll
+          for (int i = 0; i < G; ++i) e[i] = term(i, top);
+          const float t = run_sum(e);
+          sm[2 * k] += one ? 0.0f : t;
+          sm[2 * k + 1] += one ? t : 0.0f;
+        }
+      if (totals) {
+        float e[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) e[i] = term(i, mx_tot);
+        sm_tot += run_sum(e);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) rel[i] = mx[i] + Real<float>::log2(sm[i]);
+    rel_tot = mx_tot + Real<float>::log2(sm_tot);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) rel[i] = 0.0f;
+#pragma unroll 1
+    for (uint32_t left = sides; left; left &= left - 1u) {
+      const int i = __builtin_ctz(left);
+      const float x = lane_rel<D>(y, xr, a.xl, a.M, c, i >> 1, i & 1);
+#pragma unroll
+      for (int q = 0; q < 2 * NB; ++q) rel[q] = q == i ? x : rel[q];
+    }
+  }
+  double lam[2 * NB];
+#pragma unroll
+  for (int i = 0; i < 2 * NB; ++i) lam[i] = base + (double)rel[i];
+  const double lam_tot = total_slow ? (double)rel_tot : log2_wide(total);
+  double arg_t = lt_t;
+  if (total_slow && tl >= 0) arg_t = (double)(-c * rel_dot<D>(y, xr, a.xl + (int64_t)tl * D));
+  finish_frame64_outputs<NB>(m, tl, redo, side, lam, lam_tot, arg_t, llr_out, u, v);
 }
 
 // Sum of a double over the 64 lanes of a wave (every lane gets the result).
@@ -459,15 +613,58 @@ __device__ __forceinline__ double wave_sum(double x) {
   return x;
 }
 
-// ---- exact recomputation by a whole wave ------------------------------------
-// The exact path of the second tiers where few lanes of a wave need it. A lane
-// that walks a large set alone holds its wave for ~0.5 ms per item (8-D, M =
-// 2048: two passes over half the set per starved side), and the few waves
-// that hold such items end the launch alone; here the 64 lanes share each
-// pass over the points, one item after another. 8-D/2048, 1e6 samples with
-// LLRs: 484 such items at 24 dB, 3.86 -> 1.00 ms; 1969 at 25 dB, 9.01 ->
-// 1.06 ms. Same metric and reference point as the per-lane form above; the
-// sums are taken per lane and then across the lanes.
+// Moves within a row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_of(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppXor3 = 0x1b, kDppXor7 = 0x141, kDppXor8 = 0x128;
+
+// op (commutative) over the lanes of each row of 16 that agree in bit SKIP of
+// their number (SKIP > 3: over the row), in every lane; all lanes take part. In
+// each step both partners apply op to the same two values.
+template <int SKIP, typename OP>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t x, OP&& op) {
+  if (SKIP != 0) x = op(x, dpp_of<kDppXor1>(x));
+  if (SKIP != 1) x = op(x, dpp_of<kDppXor2>(x));
+  if (SKIP != 2) x = op(x, dpp_of<kDppXor7>(dpp_of<kDppXor3>(x)));
+  if (SKIP != 3) x = op(x, dpp_of<kDppXor8>(x));
+  return x;
+}
+// ... over the lanes of the wave that agree in bit SKIP (6: over all 64).
+template <int SKIP, typename OP>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, OP&& op) {
+  x = row_reduce<SKIP>(x, op);
+  if (SKIP != 4) {
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op(p[0], p[1]);
+  }
+  if (SKIP != 5) {
+    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    x = op(p[0], p[1]);
+  }
+  return x;
+}
+__device__ __forceinline__ uint32_t fadd_bits(uint32_t p, uint32_t q) {
+  return __float_as_uint(__uint_as_float(p) + __uint_as_float(q));
+}
+template <int SKIP = 6>
+__device__ __forceinline__ float wave_max_f(float x) {      // NaN only if every lane's is
+  return __uint_as_float(wave_reduce<SKIP>(__float_as_uint(x), [](uint32_t p, uint32_t q) {
+    return __float_as_uint(__builtin_fmaxf(__uint_as_float(p), __uint_as_float(q)));
+  }));
+}
+template <int SKIP = 6>
+__device__ __forceinline__ float wave_sum_f(float x) {
+  return __uint_as_float(wave_reduce<SKIP>(__float_as_uint(x), fadd_bits));
+}
+template <int SKIP = 6>
+__device__ __forceinline__ float row_sum_f(float x) {
+  return __uint_as_float(row_reduce<SKIP>(__float_as_uint(x), fadd_bits));
+}
+__device__ __forceinline__ float lane_value(float x, int l) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), l));
+}
 
 // Index of the point nearest to y (uniform); ties to the lowest.
 template <int D>
@@ -479,114 +676,226 @@ __device__ __forceinline__ int wave_nearest(const float (&y)[D], const float* __
     const float d2 = sqdist<float, D>(y, xl + (int64_t)j * D);
     if (d2 < bd) { bd = d2; best = j; }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float od = __shfl_xor(bd, off, 64);
-    const int oj = __shfl_xor(best, off, 64);
-    if (od < bd || (od == bd && oj < best)) { bd = od; best = oj; }
-  }
-  return __builtin_amdgcn_readfirstlane(best);
+  const float least = -wave_max_f(-bd);
+  // the lowest index among the lanes at the least distance
+  const uint32_t at = wave_reduce<6>(bd == least ? (uint32_t)best : 0x7fffffffu,
+                                  [](uint32_t p, uint32_t q) { return p < q ? p : q; });
+  return __builtin_amdgcn_readfirstlane((int)at);
 }
 
-// As slow_rel, for uniform y, r, k, b.
+// As slow_rel, for uniform y, r, k, b, by the whole wave: the sums are taken
+// per lane and then across the lanes.
 template <int D>
-__device__ __forceinline__ float wave_rel(const float (&y)[D], const float* __restrict__ xl, int M, float c, int r,
-                                          int k, int b) {
-  const float* xr = xl + (int64_t)r * D;
+__device__ __forceinline__ float wave_rel(const float (&y)[D], const float (&xr)[D], const float* __restrict__ xl,
+                                          int M, float c, int k, int b) {
   const int cnt = k >= 0 ? M >> 1 : M;
   const int lowmask = k >= 0 ? (1 << k) - 1 : 0;
   auto label = [&](int i) { return k >= 0 ? (((i & ~lowmask) << 1) | (b << k) | (i & lowmask)) : i; };
   const int lane = threadIdx.x & 63;
   float dmax = -__builtin_inff();
 #pragma unroll 2
-  for (int i = lane; i < cnt; i += 64) {
-    const float dj = rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c);
-    dmax = dj > dmax ? dj : dmax;
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float o = __shfl_xor(dmax, off, 64);
-    dmax = o > dmax ? o : dmax;
-  }
+  for (int i = lane; i < cnt; i += 64) dmax = __builtin_fmaxf(dmax, -c * rel_dot<D>(y, xr, xl + (int64_t)label(i) * D));
+  dmax = wave_max_f(dmax);
   float sum = 0.0f;
 #pragma unroll 2
   for (int i = lane; i < cnt; i += 64)
-    sum += Real<float>::exp2(rel_metric<float, D>(y, xr, xl + (int64_t)label(i) * D, c) - dmax);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  return dmax + Real<float>::log2(sum);
+    sum += Real<float>::exp2(__builtin_fmaf(-c, rel_dot<D>(y, xr, xl + (int64_t)label(i) * D), -dmax));
+  return dmax + Real<float>::log2(wave_sum_f(sum));
 }
 
-// Outputs of the lanes' FP32-family items (`mine`: this lane holds one) from
-// sums in the FP64 frame 2^(a + K64), as finish_item_frame64; called by all
-// lanes of a wave together.
-template <int D>
-__device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
-                                                     double total, const double (&side)[2 * kMaxBits],
-                                                     double thr64, int K64, double lt_t, float* llr_out, float& u,
-                                                     float& v) {
-  unsigned long long todo = __ballot(mine);
-  if (!todo) return;
-  // A pass costs the lanes' own form M points however many of them hold an
-  // item (and it takes the passes that any of them needs), and this one M / 64
-  // points and the exchanges per item: 3 points' worth. 1e6 samples of 4-D sets at
-  // high SNR, start / all lanes' form / this line: 64 points at 30 dB 1.19 /
-  // 1.53 / 0.71 ms, 128 at 30 dB 1.93 / 2.58 / 0.55 ms; 16 points at 28 dB 0.34 /
-  // 0.33 / 0.34 (0.56 with the line at 1 point).
-  if (__builtin_popcountll(todo) * ((a.M >> 6) + 3) >= a.M) {
-    if (mine) finish_item_frame64<D>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
-    return;
+// Both sides of label bit K < 6 from the kept metrics of a wave's points
+// (point lane + 64 p in lane `lane`): the lanes of a side reduce among
+// themselves. RUNS: a row holds a run of 16 labels; the runs are added in turn.
+template <int K, bool RUNS, int P>
+__device__ __forceinline__ void kept_sides(const float (&dot)[P], int M, float c, float (&rel)[2]) {
+  const int lane = threadIdx.x & 63;
+  float top = -__builtin_inff();
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (lane + 64 * p < M) top = __builtin_fmaxf(top, -c * dot[p]);
+  top = wave_max_f<K>(top);
+  float e[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    e[p] = lane + 64 * p < M ? Real<float>::exp2(__builtin_fmaf(-c, dot[p], -top)) : 0.0f;
+  float s0 = 0.0f, s1 = 0.0f;
+  if constexpr (RUNS) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      if (64 * p < M) {
+        const float t = row_sum_f<K>(e[p]);
+#pragma unroll
+        for (int l = 0; l < 64; l += 16) {
+          if (K < 4) {
+            s0 += lane_value(t, l);
+            s1 += lane_value(t, l | (1 << (K & 3)));
+          } else if ((l >> K) & 1) {
+            s1 += lane_value(t, l);
+          } else {
+            s0 += lane_value(t, l);
+          }
+        }
+      }
+    }
+  } else {
+    float sum = 0.0f;
+#pragma unroll
+    for (int p = 0; p < P; ++p) sum += e[p];
+    sum = wave_sum_f<K>(sum);
+    s0 = lane_value(sum, 0);
+    s1 = lane_value(sum, 1 << K);
   }
+  rel[0] = lane_value(top, 0) + Real<float>::log2(s0);
+  rel[1] = lane_value(top, 1 << K) + Real<float>::log2(s1);
+}
+
+// One selection of the kept metrics (k: a label bit from 6 on, or -1 for all points).
+template <bool RUNS, int P>
+__device__ __forceinline__ float kept_rel(const float (&dot)[P], int M, float c, int k, int b) {
+  const int lane = threadIdx.x & 63;
+  float top = -__builtin_inff(), sum = 0.0f;
+  auto in = [&](int p) { return lane + 64 * p < M && (k < 0 || ((p >> (k - 6)) & 1) == b); };
+#pragma unroll
+  for (int p = 0; p < P; ++p) top = in(p) ? __builtin_fmaxf(top, -c * dot[p]) : top;
+  top = wave_max_f(top);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const float e = in(p) ? Real<float>::exp2(__builtin_fmaf(-c, dot[p], -top)) : 0.0f;
+    if constexpr (RUNS) {
+      const float t = row_sum_f(e);
+#pragma unroll
+      for (int l = 0; l < 64; l += 16) sum += lane_value(t, l);
+    } else {
+      sum += e;
+    }
+  }
+  if constexpr (!RUNS) sum = wave_sum_f(sum);
+  return top + Real<float>::log2(sum);
+}
+
+// The items of a wave's lanes (`mine`: this lane holds one), one after another
+// by the whole wave. A lane that walks a large set alone holds its wave for
+// ~0.5 ms per item (8-D, M = 2048), and the few waves with such items end the
+// launch alone: 8-D/2048, 1e6 samples with LLRs, 484 such items at 24 dB, 3.86 ->
+// 1.00 ms; 1969 at 25 dB, 9.01 -> 1.06 ms. Up to 256 points each lane keeps its
+// points' metrics for all entries.
+template <typename T, T V>
+struct Const {
+  static constexpr T value = V;
+};
+template <int D, int NB, bool ALL>
+__device__ __forceinline__ void finish_items_by_wave(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
+                                                     double total, const double (&side)[2 * kMaxBits], double thr64,
+                                                     int K64, double lt_t, float* llr_out, float& u, float& v) {
   const int m = a.m;
+  const float c = a.c;
   const int lane = threadIdx.x & 63;
   double mem[2 * kMaxBits];      // logarithms of the recomputed entries
   const uint32_t redo = mine ? exact_entries<double>(total, side, m, thr64) : 0u;
   const bool total_slow = !(total >= thr64);
-  double lam_tot = log2_wide(total), delta_t = 0.0;
+  double lam_tot = log2_wide(total), arg_t = lt_t;
+  constexpr int kKept = 4;       // points per lane whose metrics are kept
+  unsigned long long todo = __ballot(mine);
   while (todo) {
     const int src = __builtin_ctzll(todo);
     todo &= todo - 1ull;
     const int64_t ns = (int64_t)(((uint64_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)n >> 32), src) << 32) |
                                  (uint32_t)__builtin_amdgcn_readlane((uint32_t)n, src));
     const int ts = __builtin_amdgcn_readlane(tl, src);
-    uint32_t rs = __builtin_amdgcn_readlane(redo, src);
+    uint32_t left = __builtin_amdgcn_readlane(redo, src);
     const bool all = __builtin_amdgcn_readlane(total_slow ? 1 : 0, src) != 0;
     float y[D];
     reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, ns, ts, y);
     const int r = wave_nearest<D>(y, a.xl, a.M);
-    const double base =
-        all ? 0.0 : (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
+    float xr[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) xr[d] = a.xl[(int64_t)r * D + d];
+    const double base = all ? 0.0 : (double)K64 - (double)c * (double)sqdist<float, D>(y, xr);
     if (all && ts >= 0) {
-      const double dt = (double)rel_metric<float, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)ts * D, a.c);
-      if (lane == src) delta_t = dt;
+      const double dt = (double)(-c * rel_dot<D>(y, xr, a.xl + (int64_t)ts * D));
+      if (lane == src) arg_t = dt;
     }
-    // the total (entry -1) if it is starved, then the starved sides
-    int i = all ? -1 : __builtin_ctz(rs | 0x80000000u);
-    while (i < 2 * m) {
-      const double lam = base + (double)wave_rel<D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1);
+    // entry i of the item: the total (-1) or a bit side
+    auto put = [&](int i, float rel) {
+      const double lam = base + (double)rel;
       if (lane == src) {
         if (i < 0) lam_tot = lam;
         else mem[i] = lam;
       }
-      if (i >= 0) rs &= rs - 1u;
-      i = __builtin_ctz(rs | 0x80000000u);
-    }
-  }
-  if (mine) {
-    double acc = 0.0;
+    };
+    auto entries = [&](auto runs, auto points) {
+      constexpr bool RUNS = decltype(runs)::value;
+      constexpr int P = decltype(points)::value;
+      float dot[P];
 #pragma unroll
-    for (int k = 0; k < kMaxBits; ++k)
-      if (k < m) {
-        const double l0 = ((redo >> (2 * k)) & 1u) ? mem[2 * k] : log2_wide(side[2 * k]);
-        const double l1 = ((redo >> (2 * k + 1)) & 1u) ? mem[2 * k + 1] : log2_wide(side[2 * k + 1]);
-        if (llr_out) llr_out[k] = (float)(0.6931471805599453094 * (l0 - l1));
-        acc += lam_tot - (((tl >> k) & 1) ? l1 : l0);
+      for (int p = 0; p < P; ++p)
+        dot[p] = lane + 64 * p < a.M ? rel_dot<D>(y, xr, a.xl + (int64_t)(lane + 64 * p) * D) : 0.0f;
+      if (all) put(-1, kept_rel<RUNS>(dot, a.M, c, -1, 0));
+      while (left) {
+        const int i = __builtin_ctz(left), k = i >> 1;
+        if (k < 6) {
+          float rel[2];
+          switch (k) {
+            case 0: kept_sides<0, RUNS>(dot, a.M, c, rel); break;
+            case 1: kept_sides<1, RUNS>(dot, a.M, c, rel); break;
+            case 2: kept_sides<2, RUNS>(dot, a.M, c, rel); break;
+            case 3: kept_sides<3, RUNS>(dot, a.M, c, rel); break;
+            case 4: kept_sides<4, RUNS>(dot, a.M, c, rel); break;
+            default: kept_sides<5, RUNS>(dot, a.M, c, rel); break;
+          }
+          put(2 * k, rel[0]);
+          put(2 * k + 1, rel[1]);
+          left &= ~(3u << (2 * k));
+        } else {
+          put(i, kept_rel<RUNS>(dot, a.M, c, k, i & 1));
+          left &= left - 1u;
+        }
       }
-    if (tl >= 0) {
-      u = (float)(total_slow ? lam_tot - delta_t : lam_tot - lt_t);
-      v = (float)acc;
+    };
+    if (ALL || (NB > 0 && a.M <= (1 << NB))) {
+      if constexpr (NB > 0) entries(Const<bool, true>{}, Const<int, NB <= 6 ? 1 : (1 << NB) / 64>{});
+    } else if constexpr (!ALL) {
+      if (a.M <= 64 * kKept) {
+        entries(Const<bool, false>{}, Const<int, kKept>{});
+      } else {
+        if (all) put(-1, wave_rel<D>(y, xr, a.xl, a.M, c, -1, 0));
+        for (; left; left &= left - 1u) {
+          const int i = __builtin_ctz(left);
+          put(i, wave_rel<D>(y, xr, a.xl, a.M, c, i >> 1, i & 1));
+        }
+      }
     }
   }
+  if (mine) finish_frame64_outputs<kMaxBits>(m, tl, redo, side, mem, lam_tot, arg_t, llr_out, u, v);
+}
+
+// A pass costs the lanes' form M points however many items the wave has; the
+// wave's form costs each item about as much as kItemPoints of them. 600003
+// samples with LLRs on the matrix cores, each lane alone with two passes per
+// starved side / this line: 4-D/64 at 28 dB (a few items in a wave) 342 / 157 us,
+// at 34 dB (all of them) 749 / 316 us; 16-D/64 at 28 dB 2242 / 787 us, 16-D/128 (the
+// wave's form alone) 4948 / 2364 us. With the line at 4 and 8 points per item 4-D/32
+// at 28 dB 206 and 223 us, 16-D/64 at 22 dB 877 and 787 us.
+constexpr int kItemPoints = 6;
+
+// The lanes' form serves sets of up to 2^NB points: 64 in the matrix-core second
+// tiers, whose waves hold at most 32 items, 128 in the vector one (64 items);
+// NB = 0: none (larger sets; the serving kernels, which have no registers for
+// both). ALL: the kernel's sets are no larger. Called by all lanes of a wave
+// together.
+template <int D, int NB, bool ALL>
+__device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
+                                                     double total, const double (&side)[2 * kMaxBits],
+                                                     double thr64, int K64, double lt_t, float* llr_out, float& u,
+                                                     float& v) {
+  const unsigned long long items = __ballot(mine);
+  if (!items) return;
+  if constexpr (NB > 0)
+    if ((ALL || a.M <= (1 << NB)) && __builtin_popcountll(items) * kItemPoints >= a.M) {
+      if (mine) finish_item_frame64<D, NB>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
+      return;
+    }
+  finish_items_by_wave<D, NB, ALL>(a, mine, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
 }
 
 }  // namespace air

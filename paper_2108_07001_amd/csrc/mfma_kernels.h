@@ -883,7 +883,10 @@ __device__ __forceinline__ bool tier2_tile(const SampleTile<D, BF>& smp, const T
 #pragma unroll
     for (int i = 0; i < 2 * kMaxBits; ++i) side[i] = 0.0;
   }
-  finish_items_frame64<D>(ex, mine, smp.n, smp.tl, total, side, thr64, K64, log2_wide(val64(arg_t)), lout, u, v);
+  // (sets of 16, up to 64, from 128 points on, or any)
+  constexpr int NB = HALF ? 4 : (QUAD == 0 ? 6 : 0);
+  finish_items_frame64<D, NB, HALF || QUAD == 0>(ex, mine, smp.n, smp.tl, total, side, thr64, K64,
+                                                 log2_wide(val64(arg_t)), lout, u, v);
   return mine;
 }
 

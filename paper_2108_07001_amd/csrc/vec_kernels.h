@@ -389,8 +389,7 @@ __global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, con
           u = (float)(lt - lt_t);
           v = (float)vacc;
         } else {
-          // (at most 16 points: the lanes' own form of the exact path)
-          finish_item_frame64<D>(exact_args<float>(a, s), n, tl, total, side, thr64, K64, lt_t, lout, u, v);
+          finish_item_frame64<D, m>(exact_args<float>(a, s), n, tl, total, side, thr64, K64, lt_t, lout, u, v);
           ex_lane = true;
         }
       }
@@ -557,7 +556,7 @@ __global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, con
 // path. Each wave sums its samples per SNR point (non-decreasing along its
 // share), and the block reduces its waves in a fixed order.
 template <int D, int G>
-__global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const float* __restrict__ xl) {
+__global__ __launch_bounds__(kBlock, D <= 7 ? 3 : 2) void demap_vec_t2(const DemapArgs a, const float* __restrict__ xl) {
   constexpr int LG = Log2G<G>::v;
   constexpr int NL = kMaxBits - LG;
   extern __shared__ double acc_lds[];  // [waves][S][4]
@@ -734,7 +733,8 @@ __global__ __launch_bounds__(kBlock) void demap_vec_t2(const DemapArgs a, const 
         ex_lane = true;
       }
     }
-    finish_items_frame64<D>(exact_args<float>(a, s), ex_lane, n, tl, total, side, thr64, K64, lt_t, lout, u, v);
+    finish_items_frame64<D, 7, false>(exact_args<float>(a, s), ex_lane, n, tl, total, side, thr64, K64, lt_t, lout, u,
+                                      v);
     if (has && tl >= 0) {
       const double du = (double)u, dv = (double)v;
       au += du;

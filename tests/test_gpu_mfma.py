@@ -342,3 +342,52 @@ def test_short_calls_end_in_the_last_block(ctx, M, D, N, prec):
     assert torch.equal(torch.nan_to_num(s2), torch.nan_to_num(ctx.sweep(c, t, zd, snr[:1], prec=prec, llr=True)[0]))
     assert N == 1 or rec > 0
     c.close()
+
+
+@pytest.mark.parametrize("M,D", [(16, 2), (32, 3), (64, 4), (128, 4), (256, 13), (512, 6), (2048, 8)])
+@pytest.mark.parametrize("prec", PRECS + ["fp32"])
+def test_exact_items_do_not_depend_on_their_neighbours(ctx, M, D, prec):
+    # a low SNR and received points so far out that both tiers' frames starve,
+    # with every term of a sum of comparable size: an item's LLRs are the same
+    # bits whether it is the only such item of its wave, one of a few or one of 64
+    X, lab = inputs.random_constellation(M + 7 * D, M, D)
+    tx, z = inputs.random_block(M + D, M, 640, D)
+    snr = -30.0
+    es = float(np.mean(np.sum(X * X, axis=1)))
+    c2 = D * 10.0 ** (snr / 10.0) / (2.0 * es * math.log(2.0))        # metric scale, log2 units
+    far = (z / np.linalg.norm(z, axis=1, keepdims=True)).astype(np.float64) * math.sqrt(6000.0 / c2)
+    near = X[tx] + 0.1 * z.astype(np.float64)
+    c = ctx.const(X, lab)
+    out = {}
+    for k in (1, 3, 17, 64):
+        Y = near.copy()
+        for w in range(0, 640, 64):
+            Y[w:w + k] = far[w:w + k]
+        L = ctx.llr(c, to_dev(Y.astype(np.float32)), snr, prec=prec)
+        ctx.sync()
+        assert ctx.last_exact() == 10 * k
+        out[k] = L.cpu().numpy().reshape(10, 64, -1)
+        ref = oracle.evaluate(X, lab, Y.astype(np.float32).astype(np.float64), snr)
+        assert_llr(L.cpu().numpy(), ref["llr"], 1e-3)
+    for k in (1, 3, 17):
+        assert np.array_equal(out[k][:, :k], out[64][:, :k])
+
+
+@pytest.mark.parametrize("M,D", [(32, 4), (64, 2), (128, 4)])
+def test_fp32_sweep_equals_its_points_past_one_round(ctx, M, D):
+    # more samples than one round of a launch, where a sweep and a single point
+    # list them in different orders, and many exact items: the same LLR bits
+    X, lab = inputs.random_constellation(M + D, M, D)
+    tx, z = inputs.random_block(M * D, M, 600_011, D)
+    t, zd = tx_dev(tx), to_dev(z)
+    c = ctx.const(X, lab)
+    snr = np.array([27.0, 31.0])
+    st, L = ctx.sweep(c, t, zd, snr, prec="fp32", llr=True)
+    ctx.sync()
+    assert ctx.last_exact() > 1000
+    for k in (0, 1):
+        s1, L1 = ctx.sweep(c, t, zd, snr[k:k + 1], prec="fp32", llr=True)
+        ctx.sync()
+        assert torch.equal(L1[0], L[k])
+        np.testing.assert_allclose(s1[0].cpu().numpy(), st[k].cpu().numpy(), rtol=1e-12, atol=1e-12)
+    c.close()
