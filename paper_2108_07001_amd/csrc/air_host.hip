@@ -548,8 +548,12 @@ air_status run_hd(air_ctx* ctx, const air_const* c, const float* in, const uint3
   if (e != hipSuccess) return hip_fail(ctx, e, "clear counters");
   // Matrix cores for M >= 32 when the coordinates are of moderate range
   // (max |x| in [1/16, 64]: the error bound of the product tiles holds), the
-  // vector kernel otherwise; both decide as the FP32 procedure does.
-  const bool on_mfma = c->M >= 32 && c->f16_ok && c->r2max >= 0x1p-8 && c->r2max <= 0x1p12;
+  // vector kernel otherwise; both decide as the FP32 procedure does. In one
+  // dimension a distance is two operations and the points lie close: from 64
+  // points on the vector kernel's time does not depend on them (1e6 samples at 24
+  // dB, vector / matrix form: 64 points 32 / 34-36 us, 256 45 / 41-76, 1024 128 /
+  // 102-386); 32 points 30 / 31, and 30 / 17 at 40 dB.
+  const bool on_mfma = c->M >= 32 && (c->D > 1 || c->M == 32) && c->f16_ok && c->r2max >= 0x1p-8 && c->r2max <= 0x1p12;
   const int grid = on_mfma ? mfma_grid(N) : vec_grid(N, c->M);
   for (int s0 = 0; s0 < S; s0 += kMaxSnrPerLaunch) {
     const int ns = (S - s0 < kMaxSnrPerLaunch) ? S - s0 : kMaxSnrPerLaunch;

@@ -15,17 +15,26 @@
 //  - the largest tile maximum, its tile, and the second largest.
 // Where exactly one row position reaches the near range and the second tile
 // does not, the near point is unique: it is the row position in the best
-// tile, and the decision needs no distance. The other samples (about 1 % at
-// low SNR on 2048 points, fewer elsewhere) are decided by the whole wave, which
-// runs hd_kernel's procedure over all points, one stride of 64 per step.
+// tile, and the decision needs no distance. Of the other samples every near point
+// lies in a near row position (of 32 over both lane halves), and hd_kernel's
+// procedure runs on the points of those rows alone:
+//  - few such samples among the wave's 64: the wave shares the tiles of one
+//    sample after another;
+//  - many: each lane takes its own sample. From kHdPass2 tiles on a second pass
+//    over the products first finds the tiles that hold a near point in a half.
+// How many there are depends on the set: about 1 % at low SNR on 2048 points in
+// 8-D, 3 % of 256-QAM, half of 4096-QAM, most of 256-PAM and all of a set whose
+// points coincide in pairs. The two ways meet where a wave has about NT / 4 + 4
+// of them (a pass costs ~100 cycles per tile, a sample of the first way ~400).
 //
 // Bound by VALU issue: 20 maxima per 16 points and group against 128 matrix
-// cycles per tile and group pair at D = 8. The two-pass form before it (a
-// maximum pass, then every tile formed again, compared point by point, with
-// the FP32 distance of each near point) took ~50: 8-D/2048, N = 4e6, 11 SNR
-// points 17.8 -> 6.8 ms; 12-D/4096, N = 1e6, 1.00 -> 0.41-0.51 ms per SNR
-// point; 8-PSK^2 sweep (N = 1e6, 21 points) 0.42 -> 0.28 ms. At 4 dB, where
-// the wave's scans are most frequent, a point costs 1.35x one at 24 dB.
+// cycles per tile and group pair at D = 8. Against a maximum pass and a second
+// one that compares every product with the threshold for every sample: 8-D/2048,
+// N = 4e6, 11 SNR points 17.8 -> 6.8 ms; 12-D/4096, N = 1e6, 896 -> 400 us per
+// SNR point; 8-PSK^2 sweep (N = 1e6, 21 points) 420 -> 280 us; and on dense sets, N = 1e6 at
+// 24 dB: 4096-QAM 605 -> 377 us, 1024-QAM 174 -> 87, 2-D/4096 650 -> 423, 8-D/2048 in
+// pairs 452 -> 307 (with every such sample's full set scanned by the wave these
+// four took 2222, 217, 3246 and 2683 us).
 #pragma once
 #include "hd_kernels.h"
 #include "mfma_wide.h"
@@ -53,6 +62,33 @@ __device__ __forceinline__ void hd_take(float d, int l, float& bd, int& bl) {
   bd = better ? d : bd;
   bl = better ? l : bl;
 }
+
+// Row of a tile of row position e: 0 .. 15 in the lower lane half, 16 .. 31 in the upper.
+__device__ __forceinline__ int hd_row(int e) { return 8 * ((e >> 2) & 3) + 4 * (e >> 4) + (e & 3); }
+
+// hd_kernel's decision over the points label(0 .. cnt - 1) for the sample of
+// lane src, by the whole wave.
+template <int D, typename LABEL>
+__device__ __forceinline__ int hd_wave(const float (&y)[D], int src, int cnt, const float* __restrict__ xl,
+                                       LABEL&& label) {
+  float ys[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) ys[d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(y[d]), src));
+  float bd = __builtin_inff();
+  int bl = 0;
+  for (int i = threadIdx.x & 63; i < cnt; i += 64) {
+    const int l = label(i);
+    hd_take(hd_dist<D>(ys, xl + (int64_t)l * D), l, bd, bl);
+  }
+  const float least = -wave_max_f(-bd);
+  const uint32_t at = wave_reduce<6>(bd == least ? (uint32_t)bl : 0x7fffffffu,
+                                     [](uint32_t p, uint32_t q) { return p < q ? p : q; });
+  return __builtin_amdgcn_readfirstlane((int)at);
+}
+
+// Tiles from which on a second pass over the products pays for the samples
+// without a unique near point (below: every tile's near rows).
+constexpr int kHdPass2 = 8;
 
 // Bytes of the block-local copies of the coordinates and point records.
 __host__ __device__ constexpr int64_t hd_table_bytes(int M, int D) {
@@ -122,7 +158,7 @@ struct HdBest {
 // tier); lane (j, h) forms sample j of tile h, holds rows 8 (e / 4) + 4 h +
 // e % 4 of column j of both tiles' products and finishes its own sample.
 template <int D, bool TBL>
-__global__ __launch_bounds__(256, D <= 8 ? 3 : 2) void hd_mfma(const HdArgs a, const MfmaOp<false>::vec* __restrict__ rec,
+__global__ __launch_bounds__(256, D <= 4 ? 4 : (D <= 8 ? 3 : 2)) void hd_mfma(const HdArgs a, const MfmaOp<false>::vec* __restrict__ rec,
                                                 float R2) {
   typedef MfmaOp<false>::vec V;
   typedef WideOperand<D, false> OP;
@@ -236,27 +272,82 @@ __global__ __launch_bounds__(256, D <= 8 ? 3 : 2) void hd_mfma(const HdArgs a, c
       own_halves(bA.b2, bB.b2, s0, s1);
       const uint32_t rows = (uint32_t)nr[0] | ((uint32_t)nr[1] << 16);
       const bool unique = (rows & (rows - 1u)) == 0u && rows != 0u && !(__builtin_fmaxf(s0, s1) >= floor_own);
-      const int e = __builtin_ctz(rows | 0x80000000u);
-      int l_own = (int)(e < 16 ? tr[0] : tr[1]) * 32 + 8 * ((e >> 2) & 3) + 4 * (e >> 4) + (e & 3);
-      // the others (and operands out of their range): all points, by the wave
-      unsigned long long todo = __ballot(valid && (!unique || opA.ovf));
-      while (todo) {
-        const int src = __builtin_ctzll(todo);
-        todo &= todo - 1ull;
-        float ys[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-          ys[d] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(y[d]), src));
-        float bd = __builtin_inff();
-        int bl = 0;
-        for (int l = lane; l < M; l += 64) hd_take(hd_dist<D>(ys, xl + (int64_t)l * D), l, bd, bl);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-          const float od = __shfl_xor(bd, off, 64);
-          const int ol = __shfl_xor(bl, off, 64);
-          hd_take(od, ol, bd, bl);
+      int l_own = (int)(__builtin_ctz(rows | 0x80000000u) < 16 ? tr[0] : tr[1]) * 32 +
+                  hd_row(__builtin_ctz(rows | 0x80000000u));
+      // the others: the near points of each lie in its near rows (operands out
+      // of their range: anywhere)
+      unsigned long long rest = __ballot(valid && (!unique || opA.ovf));
+      if (rest) {
+        unsigned long long todo = rest & __ballot(rows != 0u && !opA.ovf);
+        rest &= ~todo;
+        if (__builtin_popcountll(todo) * 4 > (NT < kHdPass2 ? 8 : NT + 16)) {
+          // many: each lane its own sample's near rows in the tiles that hold a
+          // near point in its half, found by a second pass over the products
+          const bool mine = (todo >> lane) & 1ull;
+          float bd = __builtin_inff();
+          int bl = 0;
+          for (int t0 = 0; t0 < NT; t0 += 32) {
+            uint32_t w0 = NT < 32 ? (1u << NT) - 1u : ~0u, w1 = w0;
+            if (NT >= kHdPass2) {
+              uint32_t wA = 0u, wB = 0u;
+              const float inf = bA.inf;
+              const int nt = NT < 32 ? NT : 32;
+              V A0[NK], A1[NK];
+              load(A0, t0);
+              load(A1, t0 + 1);
+              for (int t = 0; t < nt; t += 2) {
+                const float16_t a0 = opA.product(A0), a1 = opA.product(A1);
+                const float16_t b0 = opB.product(A0), b1 = opB.product(A1);
+                const int tn = t + 2 < nt ? t0 + t + 2 : 0;
+                load(A0, tn);
+                load(A1, tn + 1);
+                asm volatile("" ::: "memory");
+                wA |= max16(a0, inf) >= fA ? 1u << t : 0u;
+                wA |= max16(a1, inf) >= fA ? 2u << t : 0u;
+                wB |= max16(b0, inf) >= fB ? 1u << t : 0u;
+                wB |= max16(b1, inf) >= fB ? 2u << t : 0u;
+              }
+              const auto w = __builtin_amdgcn_permlane32_swap(wA, wB, false, false);
+              w0 = w[0];
+              w1 = w[1];
+            }
+            if (mine) {
+              auto half = [&](uint32_t tiles, uint32_t r16, int hh) {
+                if (r16 == 0u) return;
+                for (; tiles; tiles &= tiles - 1u) {
+                  const int l0 = (t0 + __builtin_ctz(tiles)) * 32 + 4 * hh;
+                  for (uint32_t r = r16; r; r &= r - 1u) {
+                    const int l = l0 + hd_row(__builtin_ctz(r));
+                    hd_take(hd_dist<D>(y, xl + (int64_t)l * D), l, bd, bl);
+                  }
+                }
+              };
+              half(w0, rows & 0xffffu, 0);
+              half(w1, rows >> 16, 1);
+            }
+          }
+          if (mine) l_own = bl;
+        } else {
+          // few: the wave shares the tiles of one sample's near rows
+          const int lg = 31 - __builtin_clz(NT);
+          while (todo) {
+            const int src = __builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            const uint32_t rs = __builtin_amdgcn_readlane(rows, src);
+            const int bl = hd_wave<D>(y, src, __builtin_popcount(rs) << lg, xl, [&](int i) {
+              uint32_t r = rs;
+              for (int q = i >> lg; q > 0; --q) r &= r - 1u;
+              return (i & (NT - 1)) * 32 + hd_row(__builtin_ctz(r));
+            });
+            if (lane == src) l_own = bl;
+          }
         }
-        if (lane == src) l_own = bl;
+        while (rest) {
+          const int src = __builtin_ctzll(rest);
+          rest &= rest - 1ull;
+          const int bl = hd_wave<D>(y, src, M, xl, [](int i) { return i; });
+          if (lane == src) l_own = bl;
+        }
       }
       if (valid) {
         if (a.decided) a.decided[(int64_t)s * a.N + n] = a.pos[l_own];

@@ -214,3 +214,85 @@ def test_hard_decide_ties_across_tiles(ctx, M, D, twins):
     noisy = (X[a] + 0.3 * rng.standard_normal((500, D))).astype(np.float32)
     _decide_exact(ctx, X, lab, np.concatenate([mid, noisy, X[b].astype(np.float32)]),
                   np.concatenate([a, b, a]).astype(np.int64))
+
+
+def _pam(M):
+    x = 2.0 * np.arange(M) - (M - 1)
+    g = np.arange(M)
+    return (x / math.sqrt(np.mean(x * x)))[:, None].copy(), (g ^ (g >> 1)).astype(np.uint32)
+
+
+def _dense_set(name):
+    """Sets whose points lie close together for their extent: many received
+    points have several points at nearly the same distance."""
+    if name == "pam":
+        return _pam(256)
+    if name == "qam":
+        p, g = _pam(64)
+        a, b = np.meshgrid(np.arange(64), np.arange(64), indexing="ij")
+        X = np.stack([p[a.ravel(), 0], p[b.ravel(), 0]], axis=1) / math.sqrt(2.0)
+        return X, (g[a.ravel()] * 64 + g[b.ravel()]).astype(np.uint32)
+    if name == "twins":                 # every point twice, M / 2 labels apart
+        X, lab = inputs.random_constellation(91, 2048, 8)
+        pos = np.empty(2048, dtype=np.int64)
+        pos[lab] = np.arange(2048)
+        X[pos[1024:]] = X[pos[:1024]]
+        return X, lab
+    M, D = {"gauss1d32": (32, 1), "gauss2d64": (64, 2), "gauss2d256": (256, 2), "gauss2d4096": (4096, 2)}[name]
+    return inputs.random_constellation(M + D, M, D)
+
+
+@pytest.mark.parametrize("name", ["pam", "qam", "twins", "gauss1d32", "gauss2d64", "gauss2d256", "gauss2d4096"])
+@pytest.mark.parametrize("few", [False, True])
+def test_hard_decide_dense_sets(ctx, name, few):
+    # most received points without a unique near point (the second pass over
+    # the products, or every tile's near rows), and a few of them among points of
+    # the set itself taken far apart (one sample by the whole wave), with an
+    # infinite point between them
+    X, lab = _dense_set(name)
+    M, D = X.shape
+    tx, z = inputs.random_block(M + D, M, 1500, D)
+    for snr in (0.0, 26.0, 45.0):
+        Y = (X[tx] + math.sqrt(oracle.sigma2(X, snr)) * z.astype(np.float64)).astype(np.float32)
+        if few:
+            far = np.argmax(np.sum(X * X, axis=1))
+            keep = Y[::64].copy()
+            Y[:] = (X[far] * 1.3).astype(np.float32)
+            Y[::64] = keep
+            Y[70] = np.inf
+        c = ctx.const(X, lab)
+        dec, _ = ctx.hard_decide(c, to_dev(Y), tx_dev(tx))
+        ctx.sync()
+        ref = oracle.hard_decisions(X, lab, Y, tx)
+        np.testing.assert_array_equal(dec.cpu().numpy().astype(np.uint32), ref["decided"])
+        c.close()
+
+
+@pytest.mark.parametrize("name", ["pam", "qam", "twins", "gauss2d4096"])
+def test_hard_decide_dense_sets_cost(ctx, name):
+    # the matrix-core form is there to be faster than the vector kernel, which
+    # the same set takes with its coordinates a thousand times as large
+    X, lab = _dense_set(name)
+    M, D = X.shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    N = 400_000
+    tx = torch.randint(0, M, (N,), generator=g, device="cuda", dtype=torch.int32)
+    z = torch.randn((N, D), generator=g, device="cuda")
+    best = {}
+    for scale in (1.0, 1000.0):
+        Xs = X * scale
+        Y = (torch.from_numpy(Xs).cuda()[tx.long()] + math.sqrt(oracle.sigma2(Xs, 20.0)) * z.double()).float()
+        c = ctx.const(Xs, lab)
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                ctx.hard_decide(c, Y, tx)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 4)
+        best[scale] = min(times)
+        c.close()
+    assert best[1.0] <= 1.3 * best[1000.0], best
