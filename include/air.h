@@ -161,9 +161,9 @@ air_status air_sweep(air_ctx *ctx, const air_const *c, const uint32_t *tx_dev,
  * comes from one 48 MiB device array per GPU, allocated with the library's
  * code on that GPU and kept until the process ends; a launch takes as many
  * SNR points (at most 64) as fit in it: per point about 4.3 bytes per sample
- * plus up to 1.7 MB for the launch's waves (5 MB at N = 1e6). N beyond what
- * one SNR point fits (about 1.1e7 samples) returns AIR_E_INVAL before any
- * launch. Every call on a GPU shares that GPU's array: calls that can overlap
+ * plus up to 1.7 MB for the launch's waves (5 MB at N = 1e6; FP64, and FP32 sets
+ * of fewer than 32 points, use none of it). N beyond what one SNR point fits
+ * (11796480 samples; any N in FP64) returns AIR_E_INVAL before any launch. Every call on a GPU shares that GPU's array: calls that can overlap
  * on one GPU (other contexts or streams) race and must be ordered by the
  * caller. Each launch writes every
  * part of the array it reads before reading it, so nothing carries over

@@ -99,27 +99,6 @@ static const MfmaFn kMfmaBF16[kMaxD + 1] = {
 // 27.5 -> 23.0 us, 391 + 391 blocks 27.2 -> 31.6 us).
 constexpr int64_t kTailSums = 160;
 
-// Grid of a matrix-core launch: 4 waves per block, one pair of 32-sample
-// tiles (64 samples) per wave and round.
-static int mfma_grid(int64_t N) {
-  const int64_t pairs = ((N + 31) / 32 + 1) / 2;
-  const int64_t g = (pairs + 3) / 4;
-  return (int)(g < kMaxGrid ? g : kMaxGrid);
-}
-
-// Grid of a vector-kernel launch: one sample per thread and round. For the sets
-// of at most 16 points, whose samples are cheap, the per-block reductions weigh
-// more, and 1024 blocks measured faster than 1536 (2-D QAM-4 buffers of 2^20
-// symbols: 25 %); their LLR-only calls write no partial sums. Larger sets take up
-// to kMaxGrid blocks at one SNR point, and at several 1024 that the points are
-// dealt out to (8-D/2048, 1e6 samples: 5 points 4.78 -> 4.48 ms with 2 x 1024, one
-// point 0.96 -> 1.09 ms with 1024).
-static int vec_grid(int64_t N, int M = 0, bool llr_only = false, int S = 1) {
-  const int64_t cap = M > 16 ? (S > 1 ? 1024 : kMaxGrid) : (llr_only ? 2048 : 1024);
-  const int64_t g = (N + kBlock - 1) / kBlock;
-  return (int)(g < cap ? g : cap);
-}
-
 // Fixed-order reduction of the per-block partials of one launch: block s
 // reduces SNR point s (finish_point). Block 0 folds this call's error into the
 // sticky word and zeroes the next call's words.
@@ -364,7 +343,11 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   const size_t tsz = fp64 ? sizeof(double) : sizeof(float);
   // matrix-core tiles hold 16 or 32 points; smaller sets run the FP32 vector kernel
   const bool mfma = (prec == AIR_FP16X3 || prec == AIR_BF16X3) && c->M >= 16;
-  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M, !tx, S);
+  // the vector kernels' exact forms of at most 16 points finish every item in
+  // one kernel; the FP32 form of more points also has a second tier
+  const bool small = !mfma && !maxlog && c->M <= 16;
+  const bool vec_t2 = !mfma && !fp64 && !maxlog && !small;
+  const int grid = mfma ? mfma_grid(N) : vec_grid(N, c->M, S, !small || tx);
   const VecFn vfn = fp64 ? kVecF64[c->D] : kVecF32[c->D];
   const MfmaFn mfn = prec == AIR_BF16X3 ? kMfmaBF16[c->D] : kMfmaF16[c->D];
   const void* rec = prec == AIR_BF16X3 ? (const void*)c->rec_bf16 : (const void*)c->rec_f16;
@@ -381,36 +364,21 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   a.m = c->m;
   a.D = c->D;
   a.sweep = sweep;
-  // the vector kernels' exact forms of at most 16 points finish every item in
-  // one kernel; the FP32 form of more points also has a second tier
-  const bool small = !mfma && !maxlog && c->M <= 16;
-  const bool vec_t2 = !mfma && !fp64 && !maxlog && !small;
   int snr_per_launch = kMaxSnrPerLaunch;
   if (mfma || (!fp64 && !maxlog)) {
-    // per (SNR point, wave) a run of list slots, one per sample tile the wave
-    // owns (matrix cores: pairs of tiles dealt out to the waves; vector
-    // kernel: two tiles per wave and round, every slot written)
-    const int64_t ntiles = (N + 31) / 32;
-    const int64_t waves = (int64_t)grid * 4;
-    const int64_t npairs = (ntiles + 1) / 2;
-    const int64_t stride = (int64_t)grid * kBlock;
-    const int64_t tpw = mfma ? 2 * ((npairs + waves - 1) / waves) : 2 * ((N + stride - 1) / stride);
+    const ListSize ls = list_size(N, grid, mfma);
+    const int64_t waves = ls.waves, tpw = ls.tpw;
     // tile indices, sample indices (with the padding of the last tile pair)
     // and per-SNR sample counts of the two tiers are 32-bit
     if (N > ((int64_t)1 << 32) - 128) return fail(ctx, AIR_E_UNSUPPORTED, "N too large for one call");
-    if (small && !scratch) {
-      // no lists
+    const int64_t fit = scratch ? lists_that_fit(ls, (int64_t)scratch_bytes) : kMaxSnrPerLaunch;
+    if (fit < 1)
+      return fail(ctx, AIR_E_INVAL, "N too large for air_sweep_noalloc: one SNR point needs " +
+                                        std::to_string(ls.bytes()) + " bytes of its " +
+                                        std::to_string(scratch_bytes) + "-byte scratch");
+    if (small) {
+      // no lists (the same limit on N as the other forms)
     } else if (scratch) {
-      // per SNR point of a launch: list slots (8 bytes), flagged counts per
-      // wave (4) and 32 gathered sample indices per slot (4 each); three
-      // parts, each starting on a 256-byte boundary
-      const int64_t per_snr = waves * tpw * 8 + waves * 4 + waves * tpw * 32 * 4;
-      const int64_t avail = (int64_t)scratch_bytes - 3 * 256;
-      const int64_t fit = avail > 0 ? avail / per_snr : 0;
-      if (fit < 1)
-        return fail(ctx, AIR_E_INVAL, "N too large for air_sweep_noalloc: one SNR point needs " +
-                                          std::to_string(per_snr) + " bytes of its " +
-                                          std::to_string(scratch_bytes) + "-byte scratch");
       snr_per_launch = (int)(fit < kMaxSnrPerLaunch ? fit : kMaxSnrPerLaunch);
       const int64_t sl = snr_per_launch;
       auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };

@@ -18,14 +18,13 @@
 #include <stdint.h>
 
 #include "exact_rule.h"
+#include "launch_rules.h"
 
 namespace air {
 
 constexpr int kMaxSnrPerLaunch = 64;
 constexpr int kMaxBits = 12;        // M <= 4096
 constexpr int kMaxD = 16;
-constexpr int kBlock = 256;         // threads per block of the vector kernels
-constexpr int kMaxGrid = 1536;      // upper bound on blocks of one demapping launch
 
 // Where a demapping kernel is launched: the stream and, for a timed launch,
 // two events that take the kernel's own start and end times from its
@@ -58,17 +57,6 @@ struct CallWords {
   unsigned long long recomputed;   // items finished outside the first tier's sums
   unsigned long long exact;        // of those, items that needed the exact path
 };
-
-// Runs of SNR points a first-tier launch is cut into (gridDim.y), for a grid
-// of gx blocks over the samples: few samples leave most of the chip idle while
-// their waves walk all S points, so the points are dealt out until ~2048 blocks
-// exist. 1e4 samples, 41 points, with and without: 8-D/2048 964 -> 253 us, 4-D/256
-// 239 -> 71 us, 8-PSK^2 126 -> 46 us; 3e5 samples, 11 points: unchanged to 4 %
-// faster.
-inline int snr_slices(int gx, int S) {
-  const int n = 2048 / (gx > 0 ? gx : 1);
-  return n < 1 ? 1 : (n < S ? n : S);
-}
 
 // A value for, and from, another block of the same launch.
 template <typename T>

@@ -76,18 +76,6 @@ static __global__ __launch_bounds__(256) void t2_collect(const unsigned int* __r
   }
 }
 
-// Blocks of a second-tier launch over the gathered list (dealt out to the
-// waves evenly). Small sets: at most 512 (2048 waves, one round of the chip at
-// two waves per SIMD); their listed items are few, and more blocks cost more
-// than they spread. Sets of 512 points and more: as many as the first tier
-// (three rounds): of two waves that share a SIMD the older one takes most
-// issue slots, finishes at about half the time and leaves the other alone, so
-// further blocks have to follow (8-D/2048, 4e6 samples at 22 dB: 1.54 -> 1.78
-// waves per SIMD, VALU busy 81 -> 87 % of the time, sweep 16.9 -> 16.2 ms; at M
-// = 128 the items are short, and 1e6 of them took 307 us with 512 blocks, 344 us
-// with 1536).
-__host__ __device__ inline int t2_grid(int grid, int M) { return M >= 512 || grid < 512 ? grid : 512; }
-
 // The first tier's flagged samples gathered per SNR point, with their counts.
 inline void launch_t2_collect(const DemapArgs& a, int grid, hipStream_t st) {
   if (a.fin.short_lists) return;       // read by the second tier as they are
