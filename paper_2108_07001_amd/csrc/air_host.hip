@@ -355,7 +355,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
   std::memset(&a, 0, sizeof(a));
   a.in = in;
   a.tx = tx;
-  a.partials = ctx->partials;
+  a.partials.set(ctx->partials);
   a.xl = fp64 ? (const void*)c->x64 : (const void*)c->x32;
   a.lab = c->lab;
   a.N = N;
@@ -394,7 +394,7 @@ air_status run(air_ctx* ctx, const air_const* c, const void* in, const uint32_t*
       a.t2_nitem = ctx->t2_nitem;
       a.t2_items = ctx->t2_items;
     }
-    a.t2_partials = ctx->t2_partials;
+    a.t2_partials.set(ctx->t2_partials);
     a.t2_tpw = (int)tpw;
     a.t2_cap = waves * tpw * 32;
     a.t2_tot = ctx->t2_tot;

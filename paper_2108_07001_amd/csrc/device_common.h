@@ -58,15 +58,32 @@ struct CallWords {
   unsigned long long exact;        // of those, items that needed the exact path
 };
 
-// A value for, and from, another block of the same launch.
-template <typename T>
-__device__ __forceinline__ void to_other_block(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// A value from another block of the same launch, written by an atomic.
 template <typename T>
 __device__ __forceinline__ T from_other_block(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// The per-block sums of a launch, [S][4][blocks]: sum u, sum v, sum u^2, sum v^2
+// per SNR point (entry 4 s + q). The last block of a short launch reads the
+// others' (tail.h), so every access goes past the caches that blocks do not
+// share; there is no other way to the words.
+class BlockSums {
+ public:
+  void set(double* words) { p_ = words; }
+  __host__ __device__ explicit operator bool() const { return p_ != nullptr; }
+  // this block's
+  __device__ __forceinline__ void put(int entry, double v) const {
+    __hip_atomic_store(p_ + ((int64_t)entry * gridDim.x + blockIdx.x), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // block b's, of `blocks`
+  __device__ __forceinline__ double get(int entry, int b, int blocks) const {
+    return from_other_block(p_ + ((int64_t)entry * blocks + b));
+  }
+
+ private:
+  double* p_;
+};
 
 // Zeroes the words of the next call (one thread).
 __device__ inline void clear_call_words(CallWords* next) {
@@ -106,7 +123,7 @@ struct DemapArgs {
   const void* in;                   // Y (N x D) or, in sweep mode, unit noise Z (N x D)
   const uint32_t* tx;               // N transmitted indices into X, or nullptr
   void* llr;                        // [S][N][m] LLRs (nats) or nullptr
-  double* partials;                 // [S][4][gridDim.x]: sum u, sum v, sum u^2, sum v^2
+  BlockSums partials;
   int* err;                         // set to 1 when a tx index >= M is seen
   unsigned long long* recomputed;   // (sample, SNR) items finished outside the fast sums
   unsigned long long* exact;        // of those, items that needed the exact path
@@ -119,7 +136,7 @@ struct DemapArgs {
   int sweep;                        // 1: y = x_t + sigma_s z from `in`
   // second tier (matrix-core forms and the FP32 vector kernel)
   unsigned long long* t2_list;      // [S][waves][tpw]: sample tile (32 bits) | lane mask (32)
-  double* t2_partials;              // [S][4][gridDim.x], as partials, from the second tier
+  BlockSums t2_partials;            // from the second tier
   int blocks1;                      // gridDim.x of the first tier
   int t2_tpw;                       // list slots per (SNR point, wave)
   unsigned int* t2_nitem;           // [S][waves]: samples flagged in each wave's list

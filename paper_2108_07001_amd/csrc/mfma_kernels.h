@@ -929,7 +929,7 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
   const int64_t T = (int64_t)(run >> 5);
   if ((int64_t)blockIdx.x * waves >= T) {
     // no tile reaches this block: zero partials, and no tables to stage
-    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), 0.0);
+    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) a.t2_partials.put(i, 0.0);
     finish_in_last_block(a, a.blocks1);
     return;
   }
@@ -1031,7 +1031,7 @@ __global__ __launch_bounds__(256, 2) void demap_mfma_t2(const DemapArgs a,
   for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), t);
+    a.t2_partials.put(i, t);
   }
   finish_in_last_block(a, a.blocks1);
 }

@@ -974,7 +974,7 @@ __global__ __launch_bounds__(256, (MB && D <= 4) ? 3 : (D <= 12 || w_pipe<D, BF>
   for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
-    a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
+    a.partials.put(s0 * 4 + i, t);
   }
 }
 

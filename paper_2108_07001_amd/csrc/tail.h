@@ -13,7 +13,7 @@ namespace air {
 
 // Whether this block is the last of the launch to get here; every block of the
 // launch calls it once, after its last write for other blocks. Those writes
-// (to_other_block) and the last block's reads (from_other_block) go past the
+// and the last block's reads (BlockSums, which has no other access) go past the
 // caches that the blocks do not share, and a thread waits for its own before
 // it gets here. No fence: one at device scope writes back the whole L2, with
 // the LLRs in it (1e5 samples: +30 us). The ticket is zero again afterwards.
@@ -75,12 +75,10 @@ __device__ __forceinline__ void finish_in_last_block(const DemapArgs& a, int nbl
     for (int s = 0; s < a.S; ++s)
       finish_point(s, a.N, a.M, a.m, bad, a.fin.no_mi, a.fin.stats, [&](int sp, int q, int lane) {
         double t = 0.0;
-        const double* p = a.partials + ((int64_t)sp * 4 + q) * nblocks;
 #pragma unroll 4
-        for (int i = lane; i < nblocks; i += 64) t += from_other_block(p + i);
-        const double* p2 = a.t2_partials + ((int64_t)sp * 4 + q) * a.fin.blocks2;
+        for (int i = lane; i < nblocks; i += 64) t += a.partials.get(4 * sp + q, i, nblocks);
 #pragma unroll 4
-        for (int i = lane; i < a.fin.blocks2; i += 64) t += from_other_block(p2 + i);
+        for (int i = lane; i < a.fin.blocks2; i += 64) t += a.t2_partials.get(4 * sp + q, i, a.fin.blocks2);
         return t;
       });
   if (threadIdx.x == 0) {

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
   for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
-    a.partials[(int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x] = t;
+    a.partials.put(s0 * 4 + i, t);
   }
 }
 
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, con
     for (int i = threadIdx.x; i < (s1 - s0) * 4; i += blockDim.x) {
       double t = 0.0;
       for (int w = 0; w < waves; ++w) t += acc_lds[w * a.s_per * 4 + i];
-      to_other_block(a.partials + ((int64_t)(s0 * 4 + i) * gridDim.x + blockIdx.x), t);
+      a.partials.put(s0 * 4 + i, t);
     }
   if (threadIdx.x == 0) {
     if (counts[0]) atomicAdd(a.recomputed, (unsigned long long)counts[0]);
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kBlock, D <= 7 ? 3 : 2) void demap_vec_t2(const Dem
   const int64_t T = (int64_t)(run >> 6);
   if ((int64_t)blockIdx.x * waves >= T) {
     // no tile reaches this block
-    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), 0.0);
+    for (int i = threadIdx.x; i < S * 4; i += blockDim.x) a.t2_partials.put(i, 0.0);
     finish_in_last_block(a, a.blocks1);
     return;
   }
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kBlock, D <= 7 ? 3 : 2) void demap_vec_t2(const Dem
   for (int i = threadIdx.x; i < S * 4; i += blockDim.x) {
     double t = 0.0;
     for (int w = 0; w < waves; ++w) t += acc_lds[w * S * 4 + i];
-    to_other_block(a.t2_partials + ((int64_t)i * gridDim.x + blockIdx.x), t);
+    a.t2_partials.put(i, t);
   }
   finish_in_last_block(a, a.blocks1);
 }
