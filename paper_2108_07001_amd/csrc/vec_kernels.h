@@ -307,8 +307,10 @@ __global__ __launch_bounds__(kBlock) void demap_vec(const DemapArgs a, const T* 
 // PM-QPSK, 1e5 samples, 5 points 58 -> 38 us (there 16 exponentials and 9
 // logarithms of ~30 instructions each are most of it). Terms, sums and outputs
 // per item are those of demap_vec and demap_vec_t2.
+// (FP64: as many waves per SIMD as its registers allow with the exact path kept
+// within them)
 template <typename T, int D, int G>
-__global__ __launch_bounds__(kBlock) void demap_vec_small(const DemapArgs a, const T* __restrict__ xl) {
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 1 : (D <= 4 ? 4 : (D <= 11 ? 3 : 2))) void demap_vec_small(const DemapArgs a, const T* __restrict__ xl) {
   constexpr int m = Log2G<G>::v;
   constexpr bool F32 = sizeof(T) == 4;
   extern __shared__ double acc_lds[];            // [waves][s_per][4]

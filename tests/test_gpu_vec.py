@@ -285,3 +285,23 @@ def test_snr_points_dealt_out_to_blocks(ctx, M, D, prec, N, S):
         np.testing.assert_allclose(st[s].cpu().numpy(), st1[0].cpu().numpy(), rtol=1e-11, atol=1e-13)
         np.testing.assert_allclose(ml[s].cpu().numpy(), ml1[0].cpu().numpy(), rtol=1e-11, atol=1e-13)
     c.close()
+
+
+@pytest.mark.parametrize("M,D,snr", [(4, 1, 40.0), (16, 4, 36.0), (32, 2, 34.0), (64, 1, 36.0), (128, 4, 31.0),
+                                     (512, 8, 27.0), (4096, 8, 25.0), (2048, 12, 22.0)])
+def test_fp64_exact_path(ctx, M, D, snr):
+    # waves whose lanes have starved sides on either side of a bit, on one side
+    # only, and (points far outside the set) on both with a starved total
+    X, lab = inputs.random_constellation(M + D, M, D)
+    tx, z = inputs.random_block(M - D, M, 700, D, f64=True)
+    Y = X[tx] + math.sqrt(oracle.sigma2(X, snr)) * z
+    Y[64:67] += 40.0
+    Y[130:190] -= 60.0
+    c = ctx.const(X, lab)
+    stats, L = ctx.mi_gmi(c, to_dev(Y, torch.float64), tx_dev(tx), snr, prec="fp64", llr=True)
+    ctx.sync()
+    assert ctx.last_exact() >= 63
+    ref = oracle.evaluate(X, lab, Y, snr, tx=tx)
+    assert_llr(L.cpu().numpy(), ref["llr"], FP64_TOL)
+    np.testing.assert_allclose(stats.cpu().numpy(), ref["stats"], rtol=FP64_TOL, atol=FP64_TOL)
+    c.close()
