@@ -394,7 +394,7 @@ __device__ __forceinline__ bool finish_item(const ExactArgs<T>& a, int64_t n, in
 #pragma unroll
   for (int i = 0; i < 2 * kMaxBits; ++i)
     if (i < 2 * m) slow |= !(side[i] >= thr);
-  if (!slow) {
+  if (__builtin_expect(!slow, 1)) {
     finish_fast<T>(m, tl, total, side, arg_t, llr_out, u, v);
   } else {
     T mem[2 * kMaxBits];
@@ -477,6 +477,35 @@ __device__ __forceinline__ void finish_frame64_outputs(int m, int tl, uint32_t r
     u = (float)(lam_tot - arg_t);
     v = (float)acc;
   }
+}
+
+// This lane's item of a set of at most 16 points (demap_vec_small): a pass per
+// starved entry in rolled loops, which leaves the kernel its registers (8-QAM:
+// 78 against 99 with the form below, six waves per SIMD against four).
+template <int D>
+__device__ __forceinline__ void finish_small_item64(const ExactArgs<float>& a, int64_t n, int tl, double total,
+                                                    const double (&side)[2 * kMaxBits], double thr64, int K64,
+                                                    double lt_t, float* llr_out, float& u, float& v) {
+  const int m = a.m;
+  float y[D];
+  reload_point<float, D>(a.in, a.sweep, a.xl, a.sigma, n, tl, y);
+  const int r = slow_nearest<float, D>(y, a.xl, a.M);
+  const bool total_slow = !(total >= thr64);
+  const double base =
+      total_slow ? 0.0 : (double)K64 - (double)a.c * (double)sqdist<float, D>(y, a.xl + (int64_t)r * D);
+  const uint32_t redo = exact_entries<double>(total, side, m, thr64);
+  double lam_tot = log2_wide(total), arg_t = lt_t;
+  double mem[2 * kMaxBits];      // logarithms of the recomputed entries; entry -1: the total
+#pragma unroll 1
+  for (int i = total_slow ? -1 : 0; i < 2 * m; ++i)
+    if (i < 0 || ((redo >> i) & 1u)) {
+      const double lam = base + (double)slow_rel<float, D>(y, a.xl, a.M, a.c, r, i < 0 ? -1 : i >> 1, i & 1);
+      if (i < 0) lam_tot = lam;
+      else mem[i] = lam;
+    }
+  if (total_slow && tl >= 0)
+    arg_t = (double)rel_metric<float, D>(y, a.xl + (int64_t)r * D, a.xl + (int64_t)tl * D, a.c);
+  finish_frame64_outputs<kMaxBits>(m, tl, redo, side, mem, lam_tot, arg_t, llr_out, u, v);
 }
 
 // Pairs, quads, eights, ... of e[0 .. N).
@@ -914,7 +943,9 @@ __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, 
                                                      double thr64, int K64, double lt_t, float* llr_out, float& u,
                                                      float& v) {
   const unsigned long long items = __ballot(mine);
-  if (!items) return;
+  // (the usual case, said so: the scalars that the exact path has no room for are
+  // then spilled around it and not in the kernel's point loop)
+  if (__builtin_expect(items == 0ull, 1)) return;
   if constexpr (NB > 0)
     if ((ALL || a.M <= (1 << NB)) && __builtin_popcountll(items) * kItemPoints >= a.M) {
       if (mine) finish_item_frame64<D, NB>(a, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);

@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 1 : (D <= 4 ? 4 : (D <= 11
           u = (float)(lt - lt_t);
           v = (float)vacc;
         } else {
-          finish_item_frame64<D, m>(exact_args<float>(a, s), n, tl, total, side, thr64, K64, lt_t, lout, u, v);
+          finish_small_item64<D>(exact_args<float>(a, s), n, tl, total, side, thr64, K64, lt_t, lout, u, v);
           ex_lane = true;
         }
       }
@@ -557,8 +557,14 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 1 : (D <= 4 ? 4 : (D <= 11
 // values); entries still below the frame's starvation bound take the exact
 // path. Each wave sums its samples per SNR point (non-decreasing along its
 // share), and the block reduces its waves in a fixed order.
+//
+// At most 7 dimensions are held to the registers of three waves per SIMD, and 10
+// and 16 to those of two, which they would miss; the others stay below by
+// themselves, and a bound makes their point loop 5 % slower (12-D/4096, few items:
+// 577 against 606 us).
+constexpr int vec_t2_waves(int D) { return D <= 7 ? 3 : (D == 10 || D == 16 ? 2 : 1); }
 template <int D, int G>
-__global__ __launch_bounds__(kBlock, D <= 7 ? 3 : 2) void demap_vec_t2(const DemapArgs a, const float* __restrict__ xl) {
+__global__ __launch_bounds__(kBlock, vec_t2_waves(D)) void demap_vec_t2(const DemapArgs a, const float* __restrict__ xl) {
   constexpr int LG = Log2G<G>::v;
   constexpr int NL = kMaxBits - LG;
   extern __shared__ double acc_lds[];  // [waves][S][4]
