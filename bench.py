@@ -42,7 +42,7 @@ FEC_THRESHOLD = [3.8e-3, 2.0e-2]
 # unchanged.
 FIRST_TIER_SOURCES = ("device_common.h", "mfma_kernels.h", "mfma_wide.h", "mfma_inst_f16_0.hip",
                       "mfma_inst_bf16_0.hip", "vec_kernels.h", "vec_inst_f32_0.hip", "air_host.hip",
-                      "host_state.h", "tier2_list.h", "tail.h", "exact_rule.h")
+                      "host_state.h", "tier2_list.h", "tail.h", "exact_rule.h", "launch_rules.h")
 
 
 def source_hash() -> str:
@@ -148,7 +148,7 @@ def kernel_name(M: int, D: int, prec: str, tier: int) -> str:
     """A matrix-core demapping kernel as the profiler prints it. First tier:
     demap_mfma_w<D, bfloat16 operands, tables in LDS, exact-size log2 M or 0,
     max-log>; second tier: demap_mfma_t2<D, bfloat16, 16-point tiles, tables
-    in LDS>. The tables go to LDS when they take at most 40 KB (labels, FP32
+    in LDS, four tiles per step>. The tables go to LDS when they take at most 40 KB (labels, FP32
     coordinates and the point records, as the library lays them out)."""
     bf = prec == "bf16x3"
     feat = 6 * D + 6 if bf else 3 * D + 3
@@ -159,7 +159,8 @@ def kernel_name(M: int, D: int, prec: str, tier: int) -> str:
         mb = {16: 4, 32: 5, 64: 6}.get(M, 0)
         return f"demap_mfma_w<{D}, {b}, {'true' if (tbl or mb) else 'false'}, {mb}, false>"
     half = M == 16
-    return f"demap_mfma_t2<{D}, {b}, {'true' if half else 'false'}, {'true' if (half or tbl) else 'false'}>"
+    return (f"demap_mfma_t2<{D}, {b}, {'true' if half else 'false'}, {'true' if (half or tbl) else 'false'}, "
+            f"{'true' if M >= 128 else 'false'}>")
 
 
 def profile_suffix(config: str, prec: str, tier: int) -> str:

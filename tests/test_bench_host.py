@@ -3,8 +3,13 @@ rocprofv3 FETCH_SIZE / WRITE_SIZE readings into bytes per launch."""
 import csv
 import json
 import os
+import shutil
+import subprocess
+
+import pytest
 
 import bench
+from paper_2108_07001_amd import build
 
 FIELDS = ["Correlation_Id", "Dispatch_Id", "Agent_Id", "Queue_Id", "Process_Id", "Thread_Id",
           "Grid_Size", "Kernel_Id", "Kernel_Name", "Workgroup_Size", "LDS_Block_Size", "Scratch_Size",
@@ -56,3 +61,16 @@ def test_stored_traffic_follows_the_source_hash(tmp_path, monkeypatch):
     p.write_text(json.dumps({"bytes_per_launch": 123.0, "source_hash": "stale"}))
     assert bench.stored_traffic("x", "fp16x3") is None
     assert bench.stored_traffic("y", "fp16x3") is None
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="no nm")
+def test_kernel_names_are_those_of_the_library():
+    # the names by which the counter summaries pick their kernel
+    if not os.path.exists(build.LIB):
+        build.build()
+    names = subprocess.run(["nm", "-C", build.LIB], check=True, capture_output=True, text=True).stdout
+    for M, D in ((16, 2), (32, 3), (64, 4), (128, 13), (256, 4), (2048, 8), (4096, 12)):
+        for prec in ("fp16x3", "bf16x3"):
+            for tier in (1, 2):
+                k = bench.kernel_name(M, D, prec, tier)
+                assert f"{k}(" in names, k
