@@ -43,14 +43,14 @@ inline void launch_kernel(const Launch& l, F kernel, dim3 grid, dim3 block, uint
     hipLaunchKernelGGL(kernel, grid, block, shmem, l.stream, args...);
 }
 
-// Per-call device words: the tx-range error of a call and the number of items
-// sent through the exact path; zero when the call starts.
 // Sets the context's error flag, which the host reads (host memory: a plain
 // store; every writer stores the same value).
 __device__ __forceinline__ void flag_sticky(int* sticky) {
   __hip_atomic_store(sticky, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Per-call device words: the tx-range error of a call and the numbers of items
+// that left the first tier; zero when the call starts.
 struct CallWords {
   int err;
   int pad;
@@ -281,13 +281,12 @@ struct ExactArgs {
   const T* xl;                      // label-ordered coordinates
   int M, m;
   T sigma, c;
-  unsigned long long* recomputed;   // count of items that took the exact path
 };
 
 template <typename T>
 __device__ __forceinline__ ExactArgs<T> exact_args(const DemapArgs& a, int s) {
   return ExactArgs<T>{static_cast<const T*>(a.in), a.sweep, static_cast<const T*>(a.xl), a.M, a.m,
-                      Real<T>::sigma(a.snr, s), Real<T>::c(a.snr, s), a.recomputed};
+                      Real<T>::sigma(a.snr, s), Real<T>::c(a.snr, s)};
 }
 
 // Outputs of one (sample, SNR) item whose fast-path sums are all above the

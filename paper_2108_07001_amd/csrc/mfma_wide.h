@@ -436,7 +436,8 @@ constexpr int kDirectRound = 48;
 // covers the point records' L2 reads); their few spills sit outside the
 // point loop. MB = log2 M for the small sets
 // compiled at their exact size (M = 16, 32, 64: every per-bit loop and the
-// point loop are then static), 0 for any M >= 32 taken at run time. The t2
+// point loop are then static), 0 for the larger ones, taken at run time: their
+// point loop takes four tiles of 32 points per step, so M >= 128. The t2
 // list and partial-sum layouts are those of demap_mfma, so the second-tier
 // kernel is shared.
 // Max-log bit sides of one sample computed directly in FP32 (the matrix-core
@@ -1007,6 +1008,8 @@ void launch_first_tier(const DemapArgs& a, const typename MfmaOp<BF>::vec* r, co
 // the first tier's kernel only.
 template <int D, bool BF>
 hipError_t launch_mfma_wide_td(const DemapArgs& a, const void* rec, int grid, const Launch& l, int part) {
+  // a power of two, as the constellation's creation checks; every form below relies on it
+  if (a.M < 16 || (a.M & (a.M - 1)) != 0 || a.m > kMaxBits) return hipErrorInvalidValue;
   const size_t acc = sizeof(double) * 4 * a.S * 4;
   const int64_t tbytes = table_bytes(a.M, D, BF);
   const bool tbl = tbytes <= 40 * 1024;

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256, 2) void serve_tier2(const JobDesc* __restrict_
     const int ntb = HALF ? 0 : m - 5;
     const SampleParams sp = job_params(jd);
     const Tables<BF> tb{jd.lab, jd.xl, static_cast<const V*>(jd.rec)};
-    const ExactArgs<float> ex{jd.in, jd.sweep, jd.xl, jd.M, m, jd.sigma, jd.c, &jd.out->recomputed};
+    const ExactArgs<float> ex{jd.in, jd.sweep, jd.xl, jd.M, m, jd.sigma, jd.c};
     int qn = 0;
     auto finish = [&]() {
       for (int b = 0; b < qn; b += 32) {
