@@ -10,8 +10,8 @@
 //   H2D copy (the slot's stream) -> demapping kernels (the context's stream)
 //   -> D2H copy of the LLRs (the slot's stream)
 //
-// With `depth` slots the copies of one buffer overlap the kernels of another
-// in both directions. The kernels of different buffers run one after another
+// With `depth` slots the copies of one buffer overlap the kernels of others; the
+// copies in and out of one slot take turns on its stream. The kernels of different buffers run one after another
 // on the context's stream, so the context's workspace is never used by two
 // launches at once, and every buffer's LLRs are bitwise those of air_llr on
 // the same data. Host buffers that are pinned (hipHostMalloc) are copied
