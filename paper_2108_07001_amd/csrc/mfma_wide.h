@@ -496,7 +496,7 @@ __device__ __forceinline__ float softplus2(float x) {
 // themselves, without a copy, and always gains (half precision, 1.5e6 samples
 // at two SNR points with LLRs: 4-D/128 141 -> 101 us, 8-D/2048 1141 -> 583,
 // 12-D/2048 1203 -> 723, 16-D/2048 2259 -> 1478; bfloat16 with its fmax 1.05-1.56x),
-// but for 16-D/128 in bfloat16 (190 -> 196); one record set above 8 dimensions,
+// but for 15-D/128 in bfloat16 (68 -> 72); one record set above 8 dimensions,
 // two spill there (12-D/128 0.75x).
 template <int D, bool BF>
 constexpr bool w_pipe(int MB, bool ML) { return MB == 0 && (ML || BF || mfma_nk(D, BF) <= 3); }

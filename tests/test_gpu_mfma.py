@@ -391,3 +391,30 @@ def test_fp32_sweep_equals_its_points_past_one_round(ctx, M, D):
         assert torch.equal(L1[0], L[k])
         np.testing.assert_allclose(s1[0].cpu().numpy(), st[k].cpu().numpy(), rtol=1e-12, atol=1e-12)
     c.close()
+
+
+@pytest.mark.parametrize("M,D", [(16, 2), (64, 4), (128, 4), (256, 5), (2048, 8)])
+@pytest.mark.parametrize("k", [1, 40, 64])
+@pytest.mark.parametrize("prec", PRECS + ["fp32"])
+def test_rates_beside_exact_items(ctx, M, D, k, prec):
+    # k exact items in a wave whose own terms are small (each received far out in
+    # the direction in which its transmitted point is the outermost), so that the
+    # rates of the block are those of its ordinary samples and hold to their own bar
+    X, lab = inputs.random_constellation(M + 3 * D, M, D)
+    tx, z = inputs.random_block(3 * M + k, M, 512, D)
+    snr = 8.0
+    Y = X[tx] + math.sqrt(oracle.sigma2(X, snr)) * z.astype(np.float64)
+    w = z[128:128 + k].astype(np.float64)
+    w /= np.linalg.norm(w, axis=1, keepdims=True)
+    tx = tx.copy()
+    tx[128:128 + k] = np.argmax(w @ X.T, axis=1)
+    Y[128:128 + k] = X[tx[128:128 + k]] + 150.0 * w
+    Y = Y.astype(np.float32)
+    c = ctx.const(X, lab)
+    stats, L = ctx.mi_gmi(c, to_dev(Y), tx_dev(tx), snr, prec=prec, llr=True)
+    ctx.sync()
+    assert ctx.last_exact() == k
+    ref = oracle.evaluate(X, lab, Y.astype(np.float64), snr, tx=tx)
+    assert_stats(stats.cpu().numpy(), ref["stats"])
+    assert_llr(L.cpu().numpy(), ref["llr"], 1e-3)
+    c.close()
