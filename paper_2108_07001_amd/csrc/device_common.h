@@ -933,8 +933,7 @@ constexpr int kItemPoints = 6;
 
 // The lanes' form serves sets of up to 2^NB points: 64 in the matrix-core second
 // tiers, whose waves hold at most 32 items, 128 in the vector one (64 items);
-// NB = 0: none (larger sets; the serving kernels, which have no registers for
-// both). ALL: the kernel's sets are no larger. Called by all lanes of a wave
+// NB = 0: none (larger sets). ALL: the kernel's sets are no larger. Called by all lanes of a wave
 // together.
 template <int D, int NB, bool ALL>
 __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, bool mine, int64_t n, int tl,
@@ -951,6 +950,22 @@ __device__ __forceinline__ void finish_items_frame64(const ExactArgs<float>& a, 
       return;
     }
   finish_items_by_wave<D, NB, ALL>(a, mine, n, tl, total, side, thr64, K64, lt_t, llr_out, u, v);
+}
+
+// The same out of line, for the serving kernels, which have no registers to
+// spare: in line 42 of the second tier's are spilled at D = 8, out of line 17, and
+// bursts of 12 to 32 jobs took 1 to 3 % longer. The sums are copied to memory for the
+// call alone.
+struct ItemOut {
+  float u, v;
+};
+template <int D, int NB, bool ALL>
+__device__ __noinline__ ItemOut finish_items_call(const ExactArgs<float>* a, bool mine, int64_t n, int tl, double total,
+                                                  const double (*side)[2 * kMaxBits], double thr64, int K64,
+                                                  double lt_t, float* llr_out) {
+  ItemOut r{0.0f, 0.0f};
+  finish_items_frame64<D, NB, ALL>(*a, mine, n, tl, total, *side, thr64, K64, lt_t, llr_out, r.u, r.v);
+  return r;
 }
 
 }  // namespace air
